@@ -2,6 +2,7 @@
 // validation, workspace layout, kernel selection and launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -552,7 +553,9 @@ int domain_bind_and_init(DomainState &d, const lbm_config *cfg, const Layout &L,
     d.partials = reinterpret_cast<double *>(d.ws + L.off_partials);
     d.steps = 0;
     d.relax.omega = 1.0 / cfg->tau;
-    d.relax.two_tau_m1 = 2.0 * cfg->tau - 1.0;
+    // (capped: omega is 0 to every digit a population can feel there, and the collision's
+    // quotient stays in range)
+    d.relax.two_tau_m1 = std::min(2.0 * cfg->tau - 1.0, 1e300);
     d.relax.rho0 = cfg->dtype != LBM_FP64 ? cfg->rho0 : 0.0;
 
     hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, s, d.flag, 64);

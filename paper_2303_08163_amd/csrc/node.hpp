@@ -107,13 +107,17 @@ __device__ __forceinline__ void node_moments(const double (&f)[Lattice<DIM>::Q],
 
 // Square root of x on [1, 4), the range of S^2 = 1 + 3 u^2 for |u| < 1.  On the
 // device: the hardware estimate of 1/sqrt(x), one coupled Goldschmidt step
-// (g -> sqrt(x), h -> 1/(2 sqrt(x))) and two Newton corrections of g with the
+// (g -> sqrt(x), h -> 1/(2 sqrt(x))) and one Newton correction of g with the
 // residual x - g^2 taken exactly by a fused multiply-add (P. Markstein,
 // "IA-64 and Elementary Functions", 2000, ch. 8; the same scheme as a general
 // double square root, without the scaling that inputs near the ends of the
-// exponent range need and this range does not).  The result is within one
-// unit in the last place.  Outside [1, 4) -- a node that has left the
-// equilibrium's domain, flagged anyway -- its value is unspecified.
+// exponent range need and this range does not).  The estimate's relative
+// error e is at most 2^-24, the Goldschmidt step's about 1.5 e^2 and the
+// correction's half the square of that, far below the rounding of its last
+// fused multiply-add: a second correction would change nothing but ties, and
+// the result is within one unit in the last place.  Outside [1, 4) -- a node
+// that has left the equilibrium's domain, flagged anyway -- its value is
+// unspecified.
 __host__ __device__ __forceinline__ double sqrt_1to4(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const double y = __builtin_amdgcn_rsq(x);
@@ -121,9 +125,7 @@ __host__ __device__ __forceinline__ double sqrt_1to4(double x) {
     const double r = fma(-g, h, 0.5);
     g = fma(g, r, g);
     h = fma(h, r, h);
-    double d = fma(-g, g, x);
-    g = fma(d, h, g);
-    d = fma(-g, g, x);
+    const double d = fma(-g, g, x);
     return fma(d, h, g);
 #else
     return sqrt(x);
@@ -131,16 +133,14 @@ __host__ __device__ __forceinline__ double sqrt_1to4(double x) {
 }
 
 // 1 / x for the density of a node (x > 0 and of order 1 inside the
-// equilibrium's domain): the hardware reciprocal estimate and two
-// Newton-Raphson steps r <- r + r (1 - x r), within one unit in the last
-// place; for x <= 0 or non-finite (a node outside the domain, flagged) the
-// value is unspecified.
+// equilibrium's domain): the hardware reciprocal estimate r0 and one
+// third-order step r0 + r0 (e + e^2), e = 1 - x r0 (at most 2^-24, so that the
+// neglected e^3 is 2^-72), within one unit in the last place; for x <= 0 or
+// non-finite (a node outside the domain, flagged) the value is unspecified.
 __device__ __forceinline__ double recip_density(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
 // Per-axis equilibrium factors g_{-1}, g_0, g_{+1} and S = sqrt(1 + 3 u^2).
@@ -153,13 +153,34 @@ __host__ __device__ __forceinline__ void axis_factors(double u, double (&g)[3], 
     g[2] = h + half_u;
 }
 
-// 2 beta with the bulk-viscosity correction at the node's largest |u_a|.
-__host__ __device__ __forceinline__ double corrected_omega(double umax, double Smax, double two_tau_m1) {
+// 2 beta with the bulk-viscosity correction at the node's largest |u_a|, as the
+// quotient num / den.
+__host__ __device__ __forceinline__ void corrected_omega_terms(double umax, double Smax, double two_tau_m1, double &num,
+                                                               double &den) {
     const double v2 = 3.0 * umax * umax;
     const double sp1 = Smax + 1.0;
     const double q = 2.0 * (Smax * Smax) * (sp1 * sp1);
     const double p = fma(q, fma(-1.5, v2, 1.0), (v2 * v2) * fma(3.0, sp1 * sp1, 1.0));
-    return (2.0 * p) / fma(two_tau_m1, q, p);
+    num = 2.0 * p;
+    den = fma(two_tau_m1, q, p);
+}
+__host__ __device__ __forceinline__ double corrected_omega(double umax, double Smax, double two_tau_m1) {
+    double num, den;
+    corrected_omega_terms(umax, Smax, two_tau_m1, num, den);
+    return num / den;
+}
+// The same for the collision.  For |u_a| < 1 den is positive and its size far
+// inside the exponent range (the host caps 2 tau - 1 at 1e300), so the
+// quotient needs none of the general division's scaling: a refined
+// reciprocal, the quotient and one correction by its exact residual, which
+// rounds as the division does but for values next to a tie (7 instructions
+// against 11 for the general sequence).
+__device__ __forceinline__ double corrected_omega_node(double umax, double Smax, double two_tau_m1) {
+    double num, den;
+    corrected_omega_terms(umax, Smax, two_tau_m1, num, den);
+    const double r = recip_density(den);
+    const double q = num * r;
+    return fma(fma(-den, q, num), r, q);
 }
 
 // Equilibrium kinds (the values of lbm_config.equilibrium).
@@ -249,7 +270,7 @@ __device__ __forceinline__ bool collide(T (&v)[Lattice<DIM>::Q], const Relax &r)
                 umax = fmax(umax, fabs(u[a]));
                 Smax = fmax(Smax, S[a]);
             }
-            omega = corrected_omega(umax, Smax, r.two_tau_m1);
+            omega = corrected_omega_node(umax, Smax, r.two_tau_m1);
         } else {
 #pragma unroll
             for (int a = 1; a < DIM; ++a)
@@ -291,8 +312,8 @@ __device__ __forceinline__ bool collide(T (&v)[Lattice<DIM>::Q], const Relax &r)
                 if (DEV)
                     feq = fma(-Lattice<DIM>::weight(i), r.rho0, feq);
                 T vi = v[i];
-                if (sizeof(T) == 4)
-                    // Widen again rather than keep the first pass's doubles alive:
+                if (sizeof(T) == 4 && DIM == 3)
+                    // Widen again rather than keep the first pass's 27 doubles alive:
                     // an empty asm hides vi's origin (no instruction is emitted and
                     // the value is unchanged), halving the registers held here.
                     asm volatile("" : "+v"(vi));
