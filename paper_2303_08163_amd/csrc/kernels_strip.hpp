@@ -1,0 +1,337 @@
+// kernels_strip.hpp -- several LBGK steps per launch with the intermediate
+// states in registers: K steps on D2Q9 (k_strip2) and on D1Q3 (k_strip1).
+//
+// A wavefront owns a strip of columns.  Its 64 lanes hold 64 NC consecutive
+// columns (NC per lane), of which the outer H on each side are halo: a
+// population moves one node per step, so the columns that are still exact
+// shrink by one on each side and step, and the inner tx = 64 NC - 2 H >= 1 are
+// the strip's own after H >= K steps.  Neighbouring strips compute the halo
+// columns again with the same per-node code, so the results are bitwise those
+// of K one-step launches.  The x neighbours come from the lanes beside by a
+// wavefront shift (one lane move per 32 bits, no LDS and no barrier).
+//
+// Domain flags are taken from the strip's own columns only: every node is
+// some strip's own at every step.
+#pragma once
+
+#include "kernels.hpp"
+
+namespace lbm {
+
+// Value of the lane above / below (0 past the end of the wavefront: those
+// columns are halo that no later step uses).
+__device__ __forceinline__ int lane_up(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ int lane_down(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
+template <bool UP, typename T>
+__device__ __forceinline__ T lane_move(T v) {
+    if constexpr (sizeof(T) == 4) {
+        const int b = __builtin_bit_cast(int, v);
+        return __builtin_bit_cast(T, UP ? lane_up(b) : lane_down(b));
+    } else {
+        const int2 b = __builtin_bit_cast(int2, v);
+        int2 r;
+        r.x = UP ? lane_up(b.x) : lane_down(b.x);
+        r.y = UP ? lane_up(b.y) : lane_down(b.y);
+        return __builtin_bit_cast(T, r);
+    }
+}
+// g[k] <- the value that the population with c_x = cx - 1 pulls into column k.
+template <typename T, int NC>
+__device__ __forceinline__ void pull_columns(const T (&f)[NC], int cx, T (&g)[NC]) {
+    if (cx == 1) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+            g[k] = f[k];
+    } else if (cx == 2) {
+        const T left = lane_move<false>(f[NC - 1]);
+#pragma unroll
+        for (int k = NC - 1; k > 0; --k)
+            g[k] = f[k - 1];
+        g[0] = left;
+    } else {
+        const T right = lane_move<true>(f[0]);
+#pragma unroll
+        for (int k = 0; k < NC - 1; ++k)
+            g[k] = f[k + 1];
+        g[NC - 1] = right;
+    }
+}
+
+struct StripArgs {
+    const void *src;  // f*(t), row-interleaved layout
+    void *dst;        // f*(t + K)
+    int nx, ny;
+    int K;            // steps per launch (k_strip1; a template parameter of k_strip2)
+    int tx, h;        // own columns per strip, halo columns on each side
+    int rows;         // own rows per wavefront (k_strip2)
+    int strips, chunks;
+    int64_t ps, rs;
+    Relax relax;
+    int *flag;
+};
+
+constexpr int kStripThreads = 256;
+
+template <typename T, int N>
+struct StripVec {
+    typedef T type __attribute__((ext_vector_type(N)));
+};
+template <typename T>
+struct StripVec<T, 1> {
+    typedef T type;
+};
+
+// One D2Q9 wavefront: the strip's own columns of the rows [y0, y0 + R), swept
+// in y.  Sweep iteration s computes step 1 at row y0 - (K - 1) + s from HBM and,
+// behind it, step j + 1 at the row below step j's (j = 1 .. K - 1): with step j's
+// row b just computed, step j + 1 at row b - 1 pulls the populations with
+// c_y = -1 from row b, c_y = 0 from row b - 1 and c_y = +1 from row b - 2, so a
+// level keeps three populations of one row and three of two rows, nine values a
+// column, in registers.  Step j + 1 starts at s = 2 j.
+template <int DT, bool CORR, int EQ, int K, int NC, bool NT, int WPE>
+__global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(WPE))) void k_strip2(StripArgs a) {
+    using T = store_t<DT>;
+    using V = typename StripVec<T, NC>::type;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63;
+    const int w = xcd_tile((int)blockIdx.x, (int)gridDim.x) * (kStripThreads / 64) + wave;
+    const int strip = w % a.strips, chunk = w / a.strips;
+    if (chunk >= a.chunks)  // uniform per wavefront; no barrier follows
+        return;
+    // (global address space from the start: a uniform base and a 32-bit lane offset
+    // then stay a scalar register pair and one vector register)
+    typedef const __attribute__((address_space(1))) char *Gin;
+    typedef __attribute__((address_space(1))) char *Gout;
+    const Gin src = (Gin)a.src;
+    const Gout dst = (Gout)a.dst;
+    const int nx = a.nx, ny = a.ny;
+    const int x0 = strip * a.tx;
+    const int y0 = chunk * a.rows, R = min(a.rows, ny - y0);
+    // columns of this lane, wrapped; a strip whose loaded columns lie inside the
+    // row moves them as one vector
+    const bool inside = x0 >= a.h && x0 - a.h + 64 * NC <= nx;
+    uint32_t xb[NC];
+    {
+        int x = (x0 - a.h + lane * NC) % nx;
+        x = x < 0 ? x + nx : x;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            xb[k] = (uint32_t)(x * (int)sizeof(T));
+            x = x + 1 == nx ? 0 : x + 1;
+        }
+    }
+    const int own = lane * NC - a.h;  // first column of the lane within the strip's own
+    const bool mine = own >= 0 && own < a.tx;
+
+    auto load_run = [&](Gin base, T (&f)[NC]) {
+        if constexpr (NC == 1) {
+            f[0] = *(const __attribute__((address_space(1))) T *)(base + xb[0]);
+        } else if (inside) {
+            const V v = *(const __attribute__((address_space(1))) V *)(base + xb[0]);
+#pragma unroll
+            for (int k = 0; k < NC; ++k)
+                f[k] = v[k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < NC; ++k)
+                f[k] = *(const __attribute__((address_space(1))) T *)(base + xb[k]);
+        }
+    };
+    const int64_t psb = a.ps * (int64_t)sizeof(T), rsb = a.rs * (int64_t)sizeof(T);  // strides in bytes
+    // the nine runs of a step-1 row: c_y = -1 from the row above, 0, +1 from below
+    int yl;  // wrapped row of the next load's c_y = 0 runs
+    // (an empty asm on the lane's byte offset, here and at the stores: its widening
+    // to 64 bits then stays beside the access, which so takes a scalar base and a
+    // 32-bit vector offset instead of a 64-bit vector address of its own)
+    auto load_row = [&](T (&f)[9][NC]) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+            asm("" : "+v"(xb[k]));
+        const int yp = yl + 1 == ny ? 0 : yl + 1, ym = yl == 0 ? ny - 1 : yl - 1;
+        const int64_t off[3] = {(int64_t)yp * rsb, (int64_t)yl * rsb, (int64_t)ym * rsb};
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            load_run(src + (off[i / 3] + i * psb), f[i]);
+        yl = yp;
+    };
+
+    const int S = R + 2 * K - 2;  // sweep iterations
+    T A[K - 1][3][NC];            // level j's last row, c_y = 0
+    T B[K - 1][2][3][NC];         // level j's last two rows, c_y = +1, by iteration parity
+    bool bad_any = false;
+
+    auto relax_row = [&](const T (&g)[9][NC], T (&o)[9][NC]) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            T f[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                f[i] = g[i][k];
+            bad_any |= collide_dt<2, DT, CORR, EQ>(f, a.relax);
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                o[i][k] = f[i];
+        }
+    };
+    int ys = y0;  // next row to store
+    auto iteration = [&](T (&in)[9][NC], int s, auto pp) {
+        constexpr int P = decltype(pp)::value;
+        T g[9][NC], o[9][NC];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            pull_columns<T, NC>(in[i], i % 3, g[i]);
+        relax_row(g, o);
+        if (s + 1 < S)  // the next row's loads, in flight during the steps below
+            load_row(in);
+#pragma unroll
+        for (int j = 0; j < K - 1; ++j) {
+            // inputs of step j + 2 from step j + 1's rows; its last rows move on
+#pragma unroll
+            for (int cx = 0; cx < 3; ++cx) {
+                pull_columns<T, NC>(o[cx], cx, g[cx]);
+                pull_columns<T, NC>(A[j][cx], cx, g[3 + cx]);
+                pull_columns<T, NC>(B[j][P][cx], cx, g[6 + cx]);
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    A[j][cx][k] = o[3 + cx][k];
+                    B[j][P][cx][k] = o[6 + cx][k];
+                }
+            }
+            if (s < 2 * (j + 1))  // uniform: the next level has not started
+                return;
+            relax_row(g, o);
+        }
+        const Gout row = dst + (int64_t)ys * rsb;
+        ++ys;
+        if (inside) {
+            if (mine) {
+                asm("" : "+v"(xb[0]));
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    const Gout base = row + i * psb;
+                    V v;
+                    if constexpr (NC == 1)
+                        v = o[i][0];
+                    else
+#pragma unroll
+                        for (int k = 0; k < NC; ++k)
+                            v[k] = o[i][k];
+                    auto *q = (__attribute__((address_space(1))) V *)(base + xb[0]);
+                    if constexpr (NT)
+                        __builtin_nontemporal_store(v, q);
+                    else
+                        *q = v;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < NC; ++k)
+                if (mine && x0 + own + k < nx)
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) {
+                        const Gout base = row + i * psb;
+                        *(__attribute__((address_space(1))) T *)(base + xb[k]) = o[i][k];
+                    }
+        }
+    };
+
+    yl = (y0 - (K - 1)) % ny;
+    yl = yl < 0 ? yl + ny : yl;
+    T in[9][NC];
+    load_row(in);
+    for (int s = 0;;) {
+        iteration(in, s, std::integral_constant<int, 0>{});
+        if (++s >= S)
+            break;
+        iteration(in, s, std::integral_constant<int, 1>{});
+        if (++s >= S)
+            break;
+    }
+    raise_flag(a.flag, bad_any && mine);
+}
+
+// One D1Q3 wavefront: K steps (1 .. h) of the strip's own columns.  h and tx are
+// multiples of NC and of the vector width.
+template <int DT, bool CORR, int EQ, int NC, bool NT>
+__global__ __launch_bounds__(kStripThreads) void k_strip1(StripArgs a) {
+    using T = store_t<DT>;
+    constexpr int VW = NC * sizeof(T) < 16 ? NC : 16 / (int)sizeof(T);
+    using V = typename StripVec<T, VW>::type;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63;
+    const int strip = xcd_tile((int)blockIdx.x, (int)gridDim.x) * (kStripThreads / 64) + wave;
+    if (strip >= a.strips)
+        return;
+    const T *__restrict__ src = static_cast<const T *>(a.src);
+    T *__restrict__ dst = static_cast<T *>(a.dst);
+    const int nx = a.nx;
+    const int x0 = strip * a.tx;
+    const bool inside = x0 >= a.h && x0 - a.h + 64 * NC <= nx;  // uniform
+    const int xl = x0 - a.h + lane * NC;                        // first column of the lane
+    T f[3][NC];
+    if (inside) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int k = 0; k < NC; k += VW) {
+                const V v = *reinterpret_cast<const V *>(src + i * a.ps + xl + k);
+#pragma unroll
+                for (int q = 0; q < VW; ++q)
+                    f[i][k + q] = v[q];
+            }
+    } else {
+        int x = xl % nx;
+        x = x < 0 ? x + nx : x;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                f[i][k] = src[i * a.ps + x];
+            x = x + 1 == nx ? 0 : x + 1;
+        }
+    }
+    bool bad = false;
+    for (int j = 0; j < a.K; ++j) {
+        T g0[NC], g2[NC];
+        pull_columns<T, NC>(f[0], 0, g0);
+        pull_columns<T, NC>(f[2], 2, g2);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            T v[3] = {g0[k], f[1][k], g2[k]};
+            bad |= collide_dt<1, DT, CORR, EQ>(v, a.relax);
+            f[0][k] = v[0];
+            f[1][k] = v[1];
+            f[2][k] = v[2];
+        }
+    }
+    const int own = lane * NC - a.h;
+    const bool mine = own >= 0 && own < a.tx;
+    raise_flag(a.flag, bad && mine);
+    if (!mine)
+        return;
+    if (inside) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int k = 0; k < NC; k += VW) {
+                V v;
+#pragma unroll
+                for (int q = 0; q < VW; ++q)
+                    v[q] = f[i][k + q];
+                V *p = reinterpret_cast<V *>(dst + i * a.ps + xl + k);
+                if constexpr (NT)
+                    __builtin_nontemporal_store(v, p);
+                else
+                    *p = v;
+            }
+    } else {
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+            if (x0 + own + k < nx)
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    dst[i * a.ps + x0 + own + k] = f[i][k];
+    }
+}
+
+}  // namespace lbm

@@ -1,5 +1,5 @@
-// kernels_t2.hpp -- several LBGK steps per launch (temporal blocking): two on
-// D2Q9, K = 2, 4 or 8 on D1Q3 (k_stream_collide_t1, further below).
+// kernels_t2.hpp -- two LBGK steps per launch on D2Q9 (temporal blocking), the
+// intermediate state in LDS.
 //
 // A step reads and writes every population once, so a one-step kernel moves
 // 2 Q s bytes per node update whatever its tiling.  Two steps in one sweep
@@ -538,103 +538,6 @@ __device__ __forceinline__ void two_step_rows_tile(const Step2Args &a, int tile,
 template <int DT, bool CORR, int EQ = kEqEntropic, bool NT = false>
 __global__ __launch_bounds__(1024) void k_stream_collide2(Step2Args a) {
     two_step_tile<DT, CORR, EQ, NT>(a, xcd_tile((int)blockIdx.x, (int)gridDim.x));
-}
-
-// ---------------------------------------------------------------------------
-// D1Q3, K steps per launch.  A workgroup owns tx consecutive nodes [x0, x0 +
-// tx) and keeps the segment [x0 - K, x0 + tx + K) in LDS, as two buffers
-// [3][tx + 2K] used in turn.  Step 1 pulls from HBM for the positions
-// 1 .. tx + 2K - 2 of the segment, step j for j .. tx + 2K - 1 - j from the
-// previous step's buffer, and step K, on the owned positions, stores to HBM:
-// a population moves one node per step, so K nodes of halo on each side are
-// all that K steps need.  The halo nodes are also computed by the
-// neighbouring workgroups, with the same per-node code, so the results are
-// bitwise those of K one-step launches.  Needs nx >= tx + K (one periodic
-// wrap); the last workgroup's positions past nx are the nodes from x = 0 on,
-// computed but not stored.
-struct StepKArgs {
-    const void *src;  // f*(t)
-    void *dst;        // f*(t + K)
-    int nx;
-    int tx;           // owned nodes per workgroup
-    int K;            // steps per launch (2 .. 8)
-    int64_t ps;       // population stride (the one row's pitch)
-    Relax relax;
-    int *flag;
-};
-
-constexpr int kT1MaxK = 8;
-
-__host__ __device__ constexpr size_t t1_lds_bytes(int tx, int K, size_t elem) {
-    return (size_t)2 * 3 * (size_t)(tx + 2 * K) * elem;
-}
-
-template <int DT, bool CORR, int EQ = kEqEntropic, bool NT = false>
-__global__ __launch_bounds__(256) void k_stream_collide_t1(StepKArgs a) {
-    using T = store_t<DT>;
-    extern __shared__ __align__(16) unsigned char t1_lds[];
-    const T *__restrict__ src = static_cast<const T *>(a.src);
-    T *__restrict__ dst = static_cast<T *>(a.dst);
-    const int w = a.tx + 2 * a.K;  // segment length
-    // the two buffers at offsets 0 and 3 w of the LDS array: offsets, not a
-    // chosen pointer, so that every access keeps the LDS address space (a
-    // pointer picked from an array of two compiles to flat accesses)
-    T *lds = reinterpret_cast<T *>(t1_lds);
-    const int x0 = (int)blockIdx.x * a.tx;
-    const int nthr = (int)blockDim.x;
-    auto wrap = [&](int x) { return x < 0 ? x + a.nx : (x >= a.nx ? x - a.nx : x); };
-
-    // step 1: positions m = 1 .. w - 2 (x = x0 - K + m) pull f*_i(x - c_i) from HBM
-    for (int m = 1 + (int)threadIdx.x; m < w - 1; m += nthr) {
-        const int x = x0 - a.K + m;
-        T f[3];
-#pragma unroll
-        for (int cx = 0; cx < 3; ++cx)
-            f[cx] = src[cx * a.ps + wrap(x + 1 - cx)];
-        const bool bad = collide_dt<1, DT, CORR, EQ>(f, a.relax);
-        raise_flag(a.flag, bad);
-        if (a.K == 1) {
-            if (m >= 1 && m < 1 + a.tx && x < a.nx)
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    dst[i * a.ps + x] = f[i];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                lds[i * w + m] = f[i];
-        }
-    }
-    // steps 2 .. K from LDS; the last one stores the owned positions
-    for (int j = 2; j <= a.K; ++j) {
-        __syncthreads();
-        const int in = j & 1 ? 3 * w : 0, out = 3 * w - in;
-        for (int m = j + (int)threadIdx.x; m < w - j; m += nthr) {
-            T f[3];
-#pragma unroll
-            for (int cx = 0; cx < 3; ++cx)
-                f[cx] = lds[in + cx * w + m + 1 - cx];
-            const bool bad = collide_dt<1, DT, CORR, EQ>(f, a.relax);
-            raise_flag(a.flag, bad);
-            if (j == a.K) {
-                const int x = x0 - a.K + m;  // m in [K, K + tx): x0 <= x < x0 + tx
-                if (x < a.nx) {
-                    if constexpr (NT) {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i)
-                            __builtin_nontemporal_store(f[i], dst + i * a.ps + x);
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i)
-                            dst[i * a.ps + x] = f[i];
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    lds[out + i * w + m] = f[i];
-            }
-        }
-    }
 }
 
 }  // namespace lbm

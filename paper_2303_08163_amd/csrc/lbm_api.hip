@@ -203,12 +203,9 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
     }
     const bool t2_fits = L.dim == 2 && layout == LBM_LAYOUT_ROWS &&
                          (cfg->dtype == LBM_FP64 || cfg->dtype == LBM_FP32_DEV) && cfg->nx >= 64;
-    // D1Q3, K steps per launch: owned nodes per workgroup (the LDS segment is 2 x 3 x
-    // (tx + 2K) elements, 25 KB at K = 8), and nx >= tx + K for a single periodic wrap:
-    // short rows take tx = nx - 8 (nx >= 16)
-    const int t1_tx = (int)std::min<int64_t>(fp32 ? 1024 : 512, cfg->nx - 8);
     const bool t1_fits = L.dim == 1 && layout == LBM_LAYOUT_ROWS &&
                          (cfg->dtype == LBM_FP64 || cfg->dtype == LBM_FP32_DEV) && cfg->nx >= 16;
+    const bool automatic = tblock == 0 && shape_default && trows == 0;
     if (tblock == 0) {
         // default: two steps per launch for large D2Q9 domains.  A workgroup sweeps its
         // rows one after another (about 1.4 us per row), so small grids lack the
@@ -218,7 +215,7 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
         const int64_t big = fp32 ? (int64_t)2048 * 2048 : (int64_t)1024 * 1024;
         tblock = t2_fits && shape_default && trows == 0 && L.n >= big ? 2 : 1;
         // D1Q3: eight steps per launch whenever the row allows it (2^27 with the
-        // correction: FP32 297 against 229 GLUPS, FP64 295 against 127; short rows are
+        // correction: FP32 464 against 229 GLUPS, FP64 427 against 127; short rows are
         // bound by launches, and eight steps take one)
         if (t1_fits && shape_default && trows == 0)
             tblock = 8;
@@ -234,7 +231,7 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
             return LBM_EINVAL;
         }
         L.tblock = tblock;
-        L.t2_tx = t1_tx;
+        L.t2_tx = strip1_cols(cfg->nx, cfg->dtype, tblock);
         L.t2_rows = 0;
         tblock = 1;  // the two-step D2Q9 checks below do not apply
     } else {
@@ -304,6 +301,9 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
         L.t2_tx = tx;
         L.t2_rows = trows;
     }
+    L.layout = layout;
+    // runs left to the library take longer strips than time_block where they pay
+    L.deep = !automatic ? 0 : L.dim == 1 ? (L.tblock > 1 ? strip1_steps(cfg->nx) : 0) : strip2_steps(cfg, L);
     L.block_x = bx;
     L.block_y = by;
     L.npt = npt;
@@ -315,7 +315,6 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
         set_error("plane_pad too large");
         return LBM_EINVAL;
     }
-    L.layout = layout;
     if (L.zhalo && layout != LBM_LAYOUT_ROWS) {
         set_error("z_halo needs the row-interleaved layout");
         return LBM_EINVAL;
@@ -477,17 +476,7 @@ int launch_step(const Layout &L, const StepArgs &args, int dtype, bool corr, hip
     return LBM_OK;
 }
 
-// Multi-step kernels by storage, correction, equilibrium and store hint.
-template <int EQ, bool NT>
-static void (*t1_kernel_nt(int dtype, bool corr))(StepKArgs) {
-    return dtype == kF64 ? (corr ? k_stream_collide_t1<kF64, true, EQ, NT> : k_stream_collide_t1<kF64, false, EQ, NT>)
-                         : (corr ? k_stream_collide_t1<kDevF64, true, EQ, NT>
-                                 : k_stream_collide_t1<kDevF64, false, EQ, NT>);
-}
-template <int EQ>
-static void (*t1_kernel(int dtype, bool corr, bool nt))(StepKArgs) {
-    return nt ? t1_kernel_nt<EQ, true>(dtype, corr) : t1_kernel_nt<EQ, false>(dtype, corr);
-}
+// Two-step kernels by storage, correction, equilibrium and store hint.
 template <int EQ, bool NT>
 static void (*t2_kernel_nt(int dtype, bool corr))(Step2Args) {
     return dtype == kF64 ? (corr ? k_stream_collide2<kF64, true, EQ, NT> : k_stream_collide2<kF64, false, EQ, NT>)
@@ -500,19 +489,8 @@ static void (*t2_kernel(int dtype, bool corr, bool nt))(Step2Args) {
 
 // Several steps in one launch (time_block > 1): src -> dst = f*(t + time_block).
 int launch_step2(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s) {
-    if (L.dim == 1) {
-        StepKArgs a{args.src, args.dst, args.nx, L.t2_tx, L.tblock, L.ps, args.relax, args.flag};
-        const bool nt = t2_nt_stores(L.buf_bytes);
-        void (*fn)(StepKArgs) = L.eq == LBM_EQ_POLY2     ? t1_kernel<kEqPoly2>(dtype, corr, nt)
-                                : L.eq == LBM_EQ_PRODUCT ? t1_kernel<kEqProduct>(dtype, corr, nt)
-                                                         : t1_kernel<kEqEntropic>(dtype, corr, nt);
-        hipLaunchKernelGGL(fn, dim3((unsigned)((args.nx + a.tx - 1) / a.tx)), dim3(256),
-                           (unsigned)t1_lds_bytes(a.tx, a.K, L.elem), s, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return hip_fail(e, "multi-step launch");
-        return LBM_OK;
-    }
+    if (L.dim == 1)
+        return launch_strip1(L, args, dtype, corr, L.tblock, s);
     Step2Args a{args.src, args.dst, args.nx, args.ny, L.t2_tx, L.t2_rows, (args.nx + L.t2_tx - 1) / L.t2_tx,
                 (args.ny + L.t2_rows - 1) / L.t2_rows, L.ps, L.rs, args.relax, args.flag};
     const bool nt = t2_nt_stores(L.buf_bytes);
@@ -825,6 +803,46 @@ static int enqueue_pair(lbm_handle *h, int cur, hipStream_t s) {
     return launch_step2(d.L, a, d.cfg.dtype, d.cfg.bulk_correction != 0, s);
 }
 
+// Enqueue one strip launch of K steps from buffer `cur`.
+static int enqueue_strip(lbm_handle *h, int cur, int K, hipStream_t s) {
+    DomainState &d = h->d;
+    StepArgs a{d.buf[cur], d.buf[cur ^ 1], (int)d.cfg.nx, (int)d.cfg.ny, 1, 0, 0,
+               d.L.ps, d.L.rs, d.relax, d.flag, 0};
+    const bool corr = d.cfg.bulk_correction != 0;
+    return d.L.dim == 1 ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
+                        : launch_strip2(d.L, a, d.cfg.dtype, corr, K, s);
+}
+
+// Steps of the next launch of a run with n steps left.  D1Q3 strips take any
+// number; D2Q9 strips 4, or 6 and 4 (FP64), so that a count that leaves 2 or 3
+// of the sixes takes two fours instead.
+static int next_steps(const Layout &L, int64_t n) {
+    if (L.deep && L.dim == 1)
+        return (int)std::min<int64_t>(n, L.deep);
+    if (L.deep == 6 && n >= 6 && !(n >= 8 && (n % 6 == 2 || n % 6 == 3)))
+        return 6;
+    if (L.deep && n >= 4)
+        return 4;
+    return n >= L.tblock ? L.tblock : 1;
+}
+
+static int enqueue_steps(lbm_handle *h, int cur, int K, hipStream_t s) {
+    if (K == 1)
+        return enqueue_step(h, cur, s);
+    if (K == h->d.L.tblock)
+        return enqueue_pair(h, cur, s);
+    return enqueue_strip(h, cur, K, s);
+}
+
+// Launches of a graph of kGraphSteps steps (even for every time_block and
+// strip length: the population buffers are back in place after a replay).
+static int graph_launches(const Layout &L) {
+    int launches = 0;
+    for (int64_t n = kGraphSteps; n > 0; n -= next_steps(L, n))
+        ++launches;
+    return launches;
+}
+
 // The graph of kGraphSteps steps starting from buffer `cur` (captured when the
 // handle is created; later calls find it).  Returns false (and turns graphs
 // off for the handle) if any graph call fails; the caller then launches
@@ -834,6 +852,10 @@ static bool step_graph(lbm_handle *h, int cur) {
         return false;
     if (h->exec[cur])
         return true;
+    if (graph_launches(h->d.L) % 2 != 0) {
+        h->graphs_off = true;
+        return false;
+    }
     hipError_t e = hipSuccess;
     if (!h->capture)
         e = hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking);
@@ -841,12 +863,13 @@ static bool step_graph(lbm_handle *h, int cur) {
         e = hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         int rc = LBM_OK;
-        // kGraphSteps steps: as many launches, or kGraphSteps / time_block launches of
-        // time_block steps (2, 4 or 8); either way an even number of buffer swaps
-        const int launches = kGraphSteps / h->d.L.tblock;
-        for (int k = 0; k < launches && rc == LBM_OK; ++k)
-            rc = h->d.L.tblock > 1 ? enqueue_pair(h, cur ^ (k & 1), h->capture)
-                                   : enqueue_step(h, cur ^ (k & 1), h->capture);
+        int at = cur;
+        for (int64_t n = kGraphSteps; n > 0 && rc == LBM_OK;) {
+            const int K = next_steps(h->d.L, n);
+            rc = enqueue_steps(h, at, K, h->capture);
+            at ^= 1;
+            n -= K;
+        }
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(h->capture, &g);
         if (e == hipSuccess && rc == LBM_OK && g) {
@@ -903,21 +926,14 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
             d.steps += kGraphSteps;  // an even count of swaps: d.cur is unchanged
         }
     }
-    if (d.L.tblock > 1) {
-        for (; s + d.L.tblock <= nsteps; s += d.L.tblock) {
-            int rc = enqueue_pair(h, d.cur, h->stream);
-            if (rc != LBM_OK)
-                return rc;
-            d.cur ^= 1;
-            d.steps += d.L.tblock;
-        }
-    }
-    for (; s < nsteps; ++s) {
-        int rc = enqueue_step(h, d.cur, h->stream);
+    while (s < nsteps) {
+        const int K = next_steps(d.L, nsteps - s);
+        int rc = enqueue_steps(h, d.cur, K, h->stream);
         if (rc != LBM_OK)
             return rc;
         d.cur ^= 1;
-        d.steps++;
+        d.steps += K;
+        s += K;
     }
     return LBM_OK;
 }

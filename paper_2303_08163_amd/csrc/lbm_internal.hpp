@@ -25,6 +25,7 @@ struct Layout {
     bool rowwave;      // one wavefront spans a whole row (vector kernels)
     int tblock;        // LBGK steps per launch (1; 2 on D2Q9; 2, 4 or 8 on D1Q3)
     int t2_tx, t2_rows;  // multi-step kernels: owned columns (nodes) and rows per workgroup
+    int deep;          // steps of the longest launch of a run (register strips; 0: tblock)
     bool zhalo;        // z-slab: each buffer holds halo planes -1 and nz around the nz planes
     int64_t plane;     // elements of one plane (rows layout: ny * rs)
     int red_blocks;    // workgroups of the moments reduction
@@ -52,6 +53,15 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out);
 int launch_step(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s, int nz,
                 const HaloArgs *halo);
 int launch_step2(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
+
+// Register-strip launches (strip.hip).
+constexpr int64_t kStrip2Nodes = 128 * 1024;  // D2Q9 domains from here on
+constexpr int64_t kStrip1Wide = 1 << 22;      // D1Q3 rows with many columns per lane
+int strip2_steps(const lbm_config *cfg, const Layout &L);
+int strip1_steps(int64_t nx);
+int strip1_cols(int64_t nx, int dtype, int K);
+int launch_strip1(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
+int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
 
 // Bind a domain to its workspace and enqueue f = f^eq(rho, u) plus the flag
 // clear; the caller synchronises and reads the flag (domain_read_flag).
