@@ -302,8 +302,6 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
         L.t2_rows = trows;
     }
     L.layout = layout;
-    // runs left to the library take longer strips than time_block where they pay
-    L.deep = !automatic ? 0 : L.dim == 1 ? (L.tblock > 1 ? strip1_steps(cfg->nx) : 0) : strip2_steps(cfg, L);
     L.block_x = bx;
     L.block_y = by;
     L.npt = npt;
@@ -338,6 +336,16 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
         return LBM_EINVAL;
     }
     L.buf_bytes = (size_t)elems * L.elem;
+    // runs left to the library take more steps per launch than time_block where they pay
+    L.deep = !automatic ? 0 : L.dim == 1 ? (L.tblock > 1 ? strip1_steps(cfg->nx) : 0)
+                          : L.dim == 2   ? strip2_steps(cfg, L)
+                                         : (sweep3_takes(cfg, L) ? 2 : 0);
+    if (L.deep && L.dim == 2) {
+        L.strip_rows[0] = strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 4);
+        L.strip_rows[1] = L.deep == 6 ? strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 6) : 0;
+    }
+    if (L.deep && L.dim == 3)
+        L.sweep3 = sweep3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem);
     L.red_blocks = (int)std::min<int64_t>(1024, (L.n + kReduceThreads - 1) / kReduceThreads);
     // workspace: buffer A | buffer B | flag block (256 B) | diag out (256 B) | partials
     L.off_buf[0] = 0;
@@ -803,26 +811,29 @@ static int enqueue_pair(lbm_handle *h, int cur, hipStream_t s) {
     return launch_step2(d.L, a, d.cfg.dtype, d.cfg.bulk_correction != 0, s);
 }
 
-// Enqueue one strip launch of K steps from buffer `cur`.
-static int enqueue_strip(lbm_handle *h, int cur, int K, hipStream_t s) {
+// Enqueue one strip or sweep launch of K steps from buffer `cur`.
+static int enqueue_deep(lbm_handle *h, int cur, int K, hipStream_t s) {
     DomainState &d = h->d;
-    StepArgs a{d.buf[cur], d.buf[cur ^ 1], (int)d.cfg.nx, (int)d.cfg.ny, 1, 0, 0,
+    StepArgs a{d.buf[cur], d.buf[cur ^ 1], (int)d.cfg.nx, (int)d.cfg.ny, (int)d.cfg.nz, 0, 0,
                d.L.ps, d.L.rs, d.relax, d.flag, 0};
     const bool corr = d.cfg.bulk_correction != 0;
-    return d.L.dim == 1 ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
-                        : launch_strip2(d.L, a, d.cfg.dtype, corr, K, s);
+    return d.L.dim == 1   ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
+           : d.L.dim == 2 ? launch_strip2(d.L, a, d.cfg.dtype, corr, K, s)
+                          : launch_sweep3(d.L, a, d.cfg.dtype, corr, s);
 }
 
 // Steps of the next launch of a run with n steps left.  D1Q3 strips take any
 // number; D2Q9 strips 4, or 6 and 4 (FP64), so that a count that leaves 2 or 3
-// of the sixes takes two fours instead.
+// of the sixes takes two fours instead; D3Q27 sweeps 2.
 static int next_steps(const Layout &L, int64_t n) {
     if (L.deep && L.dim == 1)
         return (int)std::min<int64_t>(n, L.deep);
     if (L.deep == 6 && n >= 6 && !(n >= 8 && (n % 6 == 2 || n % 6 == 3)))
         return 6;
-    if (L.deep && n >= 4)
+    if (L.deep >= 4 && n >= 4)
         return 4;
+    if (L.deep == 2 && n >= 2)
+        return 2;
     return n >= L.tblock ? L.tblock : 1;
 }
 
@@ -831,7 +842,7 @@ static int enqueue_steps(lbm_handle *h, int cur, int K, hipStream_t s) {
         return enqueue_step(h, cur, s);
     if (K == h->d.L.tblock)
         return enqueue_pair(h, cur, s);
-    return enqueue_strip(h, cur, K, s);
+    return enqueue_deep(h, cur, K, s);
 }
 
 // Launches of a graph of kGraphSteps steps (even for every time_block and

@@ -11,6 +11,12 @@
 
 namespace lbm {
 
+// Tile of a D3Q27 two-step sweep (sweep3.hip): width with halo columns, own
+// rows and planes.
+struct Sweep3Geom {
+    int w, rows, planes;
+};
+
 // Workspace layout of one domain (all offsets in bytes, 256-byte aligned).
 struct Layout {
     int dim, q;
@@ -25,7 +31,9 @@ struct Layout {
     bool rowwave;      // one wavefront spans a whole row (vector kernels)
     int tblock;        // LBGK steps per launch (1; 2 on D2Q9; 2, 4 or 8 on D1Q3)
     int t2_tx, t2_rows;  // multi-step kernels: owned columns (nodes) and rows per workgroup
-    int deep;          // steps of the longest launch of a run (register strips; 0: tblock)
+    int deep;          // steps of the longest launch of a run (strips, sweeps; 0: tblock)
+    int strip_rows[2]; // D2Q9 strips: own rows per wavefront with 4 and with 6 steps
+    Sweep3Geom sweep3; // D3Q27 sweeps
     bool zhalo;        // z-slab: each buffer holds halo planes -1 and nz around the nz planes
     int64_t plane;     // elements of one plane (rows layout: ny * rs)
     int red_blocks;    // workgroups of the moments reduction
@@ -58,10 +66,17 @@ int launch_step2(const Layout &L, const StepArgs &args, int dtype, bool corr, hi
 constexpr int64_t kStrip2Nodes = 128 * 1024;  // D2Q9 domains from here on
 constexpr int64_t kStrip1Wide = 1 << 22;      // D1Q3 rows with many columns per lane
 int strip2_steps(const lbm_config *cfg, const Layout &L);
+int strip2_rows(int64_t nx, int64_t ny, int dtype, int K);
 int strip1_steps(int64_t nx);
 int strip1_cols(int64_t nx, int dtype, int K);
 int launch_strip1(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
 int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
+
+// Two-step D3Q27 sweeps (sweep3.hip).
+constexpr size_t kSweep3Bytes = (size_t)96 << 20;  // both population buffers from here on
+bool sweep3_takes(const lbm_config *cfg, const Layout &L);
+Sweep3Geom sweep3_geom(int64_t nx, int64_t ny, int64_t nz, size_t elem);
+int launch_sweep3(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
 
 // Bind a domain to its workspace and enqueue f = f^eq(rho, u) plus the flag
 // clear; the caller synchronises and reads the flag (domain_read_flag).

@@ -29,12 +29,15 @@ int strip2_steps(const lbm_config *cfg, const Layout &L) {
     return cfg->dtype == LBM_FP64 ? 6 : 4;
 }
 
-// Row chunks of k_strip2: the count with the least estimated time.  A sweep
+// Own rows per wavefront of k_strip2: the row chunks with the least estimated
+// time.  A sweep
 // over R own rows takes R + 2 K - 2 iterations, and an iteration with w
 // wavefronts on every SIMD about 0.7 + w units (1024^2, 4 steps: 1.32 us with
 // one, 2.09 with two, 2.86 with three; one wavefront alone waits for its own
 // results).  More chunks than fit at once run in rounds.
-static int strip2_chunks(int64_t strips, int64_t ny, int K, int occ) {
+int strip2_rows(int64_t nx, int64_t ny, int dtype, int K) {
+    const int64_t strips = (nx + 63 - 2 * K) / (64 - 2 * K);
+    const int occ = strip2_occupancy(dtype, K);
     int64_t best_c = 1;
     double best = -1.0;
     for (int64_t c = 1; c <= std::max<int64_t>(1, ny / 4); c += 1 + c / 64) {
@@ -47,7 +50,7 @@ static int strip2_chunks(int64_t strips, int64_t ny, int K, int occ) {
             best_c = c;
         }
     }
-    return (int)best_c;
+    return (int)((ny + best_c - 1) / best_c);
 }
 
 template <int DT, int K, int EQ, bool NT>
@@ -77,8 +80,7 @@ int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int 
     a.h = K;
     a.tx = 64 - 2 * K;
     a.strips = (s.nx + a.tx - 1) / a.tx;
-    const int c = strip2_chunks(a.strips, s.ny, K, strip2_occupancy(dtype, K));
-    a.rows = (s.ny + c - 1) / c;
+    a.rows = L.strip_rows[K == 6];
     a.chunks = (s.ny + a.rows - 1) / a.rows;
     a.ps = L.ps;
     a.rs = L.rs;

@@ -1,0 +1,78 @@
+"""Two-step D3Q27 sweeps (the default of large periodic domains): bitwise the
+one-step-per-launch run (time_block = 1), on ragged extents, both storage
+types, every equilibrium, odd step counts and graph replays."""
+import numpy as np
+import pytest
+
+from paper_2303_08163_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _lbm():
+    from paper_2303_08163_amd import lbm
+    return lbm
+
+
+def _fields(shape, seed, umax=0.1, rho_lo=0.8, rho_hi=1.2):
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    rho = rho_lo + (rho_hi - rho_lo) * torch.rand(shape, generator=g, dtype=torch.float64, device="cuda:0")
+    u = umax * (2 * torch.rand((3,) + shape, generator=g, dtype=torch.float64, device="cuda:0") - 1)
+    return rho, u
+
+
+def _state(d):
+    import torch
+    out = torch.empty((27,) + d.shape, dtype=torch.float64, device=d.device)
+    _lbm().lbm_get_populations(d.handle, out.data_ptr())
+    return out
+
+
+CASES = [  # (nz, ny, nx), dtype, correction, equilibrium, step chunks; every one above 96 MiB of buffers
+    ((128, 128, 128), "fp32_dev", False, "entropic", (1, 2, 5, 66)),
+    ((80, 80, 80), "fp32_dev", True, "entropic", (4, 2)),
+    ((64, 64, 64), "fp64", False, "entropic", (4, 3)),
+    ((96, 96, 96), "fp64", True, "entropic", (2, 3, 66)),
+    # extents one off a tile: 32 / 64 own columns and their rows
+    ((97, 129, 129), "fp32_dev", True, "entropic", (4, 1)),
+    ((101, 95, 97), "fp64", False, "product", (4,)),
+    ((73, 127, 191), "fp32_dev", False, "poly2", (3,)),
+    ((67, 71, 161), "fp64", True, "poly2", (2,)),
+    # few planes, few rows, narrow rows (halo columns and planes wrapped onto the domain itself)
+    ((1, 512, 1024), "fp64", False, "entropic", (4, 3)),
+    ((2, 1024, 600), "fp32_dev", True, "product", (4,)),
+    ((2000, 33, 16), "fp64", False, "entropic", (2, 2)),
+    ((500, 4, 513), "fp32_dev", False, "entropic", (6,)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_sweep_equals_one_step_bitwise(case):
+    import torch
+    lbm = _lbm()
+    shape, dtype, corr, eq, chunks = CASES[case]
+    rho0, u0 = _fields(shape, 500 + case)
+    kw = dict(dtype=dtype, bulk_correction=corr, equilibrium=eq)
+    with lbm.Domain(rho0, u0, 0.55, **kw) as a, \
+            lbm.Domain(rho0, u0, 0.55, tuning=lbm.make_tuning(time_block=1), **kw) as b:
+        for n in chunks:
+            a.step(n)
+            b.step(n)
+            assert torch.equal(_state(a), _state(b)), (shape, n)
+        da, db = (d.moments(fields=False)[2] for d in (a, b))
+        assert da == db
+
+
+def test_sweep_raises_the_domain_flag_as_one_step():
+    lbm = _lbm()
+    for umax, lo, hi in ((0.99, 0.3, 2.0), (0.97, 0.5, 1.5), (0.2, 0.9, 1.1)):
+        rho0, u0 = _fields((130, 128, 128), 9, umax, lo, hi)
+        with lbm.Domain(rho0, u0, 0.5001, dtype="fp32_dev") as a, \
+                lbm.Domain(rho0, u0, 0.5001, dtype="fp32_dev", tuning=lbm.make_tuning(time_block=1)) as b:
+            for n in (2, 4):
+                a.step(n)
+                b.step(n)
+                fa = a.moments(fields=False, raise_on_domain=False)[2]["domain_error"]
+                fb = b.moments(fields=False, raise_on_domain=False)[2]["domain_error"]
+                assert fa == fb, (umax, n)
