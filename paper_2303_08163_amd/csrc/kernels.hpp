@@ -525,8 +525,38 @@ struct MomentArgs {
     int nx;
     int64_t ps, rs;
     double rho0;
-    double *partials;  // gridDim.x * kDiagFields
+    double *partials;   // gridDim.x * kDiagFields
+    unsigned *arrived;  // workgroups that have stored their partials; 0 between launches
+    const int *flag;
+    double *out;        // kDiagFields values, then the domain flag (0 or 1)
 };
+
+// The last workgroup to finish folds the others' partials, so that a reduction
+// over the domain is one launch (a second launch of one workgroup cost 3 us and
+// more).  Partials and counter go through agent-scope atomics: each workgroup's
+// stores are complete before it counts itself in, and what the last one loads
+// is what they stored, without a write-back of the L2 that holds the fields
+// just written.  Returns whether the caller is the last workgroup; `put` runs
+// in thread 0.
+template <typename Put>
+__device__ __forceinline__ bool last_workgroup(unsigned *arrived, Put put) {
+    __shared__ bool last;
+    if (threadIdx.x == 0) {
+        put();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's stores are complete
+        last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (last)  // back to zero for the next launch
+            __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return last;
+}
+__device__ __forceinline__ void put_partial(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get_partial(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -548,8 +578,9 @@ __device__ __forceinline__ double wave_min(double v) {
 }
 
 // Reduce kDiagFields values across a 256-thread workgroup in a fixed order
-// (wavefront butterflies, then the 4 wave results in index order).
-__device__ __forceinline__ void block_reduce_diag(double (&acc)[kDiagFields], double *out) {
+// (wavefront butterflies, then the 4 wave results in index order); the result
+// is thread 0's acc.
+__device__ __forceinline__ void block_reduce_diag(double (&acc)[kDiagFields]) {
     __shared__ double lds[kReduceThreads / 64][kDiagFields];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -557,26 +588,23 @@ __device__ __forceinline__ void block_reduce_diag(double (&acc)[kDiagFields], do
         acc[k] = wave_sum(acc[k]);
     acc[5] = wave_max(acc[5]);
     acc[6] = wave_min(acc[6]);
+    __syncthreads();  // (a previous reduction's readers are done)
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < kDiagFields; ++k)
             lds[wave][k] = acc[k];
     __syncthreads();
     if (threadIdx.x == 0) {
-        double r[kDiagFields];
 #pragma unroll
         for (int k = 0; k < kDiagFields; ++k)
-            r[k] = lds[0][k];
+            acc[k] = lds[0][k];
         for (int w = 1; w < kReduceThreads / 64; ++w) {
 #pragma unroll
             for (int k = 0; k < 5; ++k)
-                r[k] += lds[w][k];
-            r[5] = fmax(r[5], lds[w][5]);
-            r[6] = fmin(r[6], lds[w][6]);
+                acc[k] += lds[w][k];
+            acc[5] = fmax(acc[5], lds[w][5]);
+            acc[6] = fmin(acc[6], lds[w][6]);
         }
-#pragma unroll
-        for (int k = 0; k < kDiagFields; ++k)
-            out[k] = r[k];
     }
 }
 
@@ -612,22 +640,31 @@ __global__ __launch_bounds__(kReduceThreads) void k_moments(MomentArgs a) {
         acc[5] = fmax(acc[5], fmax(fabs(u[0]), fmax(fabs(u[1]), fabs(u[2]))));
         acc[6] = fmin(acc[6], rho);
     }
-    block_reduce_diag(acc, a.partials + (int64_t)blockIdx.x * kDiagFields);
-}
-
-// Second pass: one workgroup folds the per-workgroup partials in a fixed order.
-static __global__ __launch_bounds__(kReduceThreads) void k_reduce_partials(const double *partials, int count,
-                                                                    double *out) {
-    double acc[kDiagFields] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, INFINITY};
-    for (int b = threadIdx.x; b < count; b += blockDim.x) {
-        const double *p = partials + (int64_t)b * kDiagFields;
+    block_reduce_diag(acc);
+    if (!last_workgroup(a.arrived, [&] {
+            double *p = a.partials + (int64_t)blockIdx.x * kDiagFields;
+#pragma unroll
+            for (int k = 0; k < kDiagFields; ++k)
+                put_partial(p + k, acc[k]);
+        }))
+        return;
+    // the partials of every workgroup in a fixed order
+    double tot[kDiagFields] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, INFINITY};
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x) {
+        const double *p = a.partials + (int64_t)b * kDiagFields;
 #pragma unroll
         for (int k = 0; k < 5; ++k)
-            acc[k] += p[k];
-        acc[5] = fmax(acc[5], p[5]);
-        acc[6] = fmin(acc[6], p[6]);
+            tot[k] += get_partial(p + k);
+        tot[5] = fmax(tot[5], get_partial(p + 5));
+        tot[6] = fmin(tot[6], get_partial(p + 6));
     }
-    block_reduce_diag(acc, out);
+    block_reduce_diag(tot);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < kDiagFields; ++k)
+            a.out[k] = tot[k];
+        a.out[kDiagFields] = __hip_atomic_load(a.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ? 1.0 : 0.0;
+    }
 }
 
 // Quadratic acoustic energy about a reference state (rho_ref, U), summed over
@@ -641,13 +678,16 @@ struct EnergyArgs {
     double rho0;  // deviation reference of the storage (0 for FP64 storage)
     double rho_ref;
     double U[3];
-    double *partials;  // gridDim.x values
+    double *partials;   // gridDim.x values
+    unsigned *arrived;  // as in MomentArgs
+    double *out;
 };
 
 __device__ __forceinline__ double block_sum(double v) {
     __shared__ double lds[kReduceThreads / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     v = wave_sum(v);
+    __syncthreads();  // (a previous reduction's readers are done)
     if (lane == 0)
         lds[wave] = v;
     __syncthreads();
@@ -683,19 +723,15 @@ __global__ __launch_bounds__(kReduceThreads) void k_energy(EnergyArgs a) {
         const double dr = rho - a.rho_ref;
         acc += fma(0.5 * a.rho_ref, du2, (dr * dr) * half_cs2_over_rho);
     }
-    const double r = block_sum(acc);
+    double r = block_sum(acc);
+    if (!last_workgroup(a.arrived, [&] { put_partial(a.partials + blockIdx.x, r); }))
+        return;
+    acc = 0.0;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x)
+        acc += get_partial(a.partials + b);
+    r = block_sum(acc);
     if (threadIdx.x == 0)
-        a.partials[blockIdx.x] = r;
-}
-
-static __global__ __launch_bounds__(kReduceThreads) void k_sum_partials(const double *partials, int count,
-                                                                        double *out) {
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < count; b += blockDim.x)
-        acc += partials[b];
-    const double r = block_sum(acc);
-    if (threadIdx.x == 0)
-        *out = r;
+        *a.out = r;
 }
 
 struct ExportArgs {

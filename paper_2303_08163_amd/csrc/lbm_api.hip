@@ -569,29 +569,32 @@ int domain_read_flag(const DomainState &d, hipStream_t s, int *flag) {
     return LBM_OK;
 }
 
-int domain_moments(DomainState &d, hipStream_t s, double *rho, double *u, lbm_diag *diag) {
+int domain_moments(DomainState &d, hipStream_t s, double *rho, double *u, lbm_diag *diag, double *host) {
     const Layout &L = d.L;
     const bool dev = d.cfg.dtype != LBM_FP64;
-    MomentArgs ma{d.buf[d.cur], rho, u, L.n, (int)d.cfg.nx, L.ps, L.rs, d.relax.rho0, d.partials};
+    // the kernel stores its result in pinned host memory, so that nothing is copied after
+    // it; without any (host NULL) in device memory
+    MomentArgs ma{d.buf[d.cur], rho,          u,         L.n,    (int)d.cfg.nx,
+                  L.ps,         L.rs,         d.relax.rho0, d.partials, reinterpret_cast<unsigned *>(d.flag + 1),
+                  d.flag,       host ? host : d.diag_dev};
     dim3 grid((unsigned)L.red_blocks), block(kReduceThreads);
     void (*mom_fn)(MomentArgs) = L.dim == 1   ? (dev ? k_moments<1, true> : k_moments<1, false>)
                                  : L.dim == 2 ? (dev ? k_moments<2, true> : k_moments<2, false>)
                                               : (dev ? k_moments<3, true> : k_moments<3, false>);
     hipLaunchKernelGGL(mom_fn, grid, block, 0, s, ma);
-    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(kReduceThreads), 0, s, (const double *)d.partials,
-                       L.red_blocks, d.diag_dev);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return hip_fail(e, "moments launch");
-    double v[kDiagFields];
-    int flag = 0;
-    e = hipMemcpyAsync(v, d.diag_dev, sizeof(v), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&flag, d.flag, sizeof(int), hipMemcpyDeviceToHost, s);
+    double v[kDiagFields + 1];
+    if (!host)
+        e = hipMemcpyAsync(v, d.diag_dev, sizeof(v), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess)
         return hip_fail(e, "moments synchronise");
+    if (host)
+        std::memcpy(v, host, sizeof(v));
+    const bool flag = v[kDiagFields] != 0.0;
     if (diag) {
         diag->mass = v[0];
         diag->momentum[0] = v[1];
@@ -631,16 +634,15 @@ int domain_export(DomainState &d, hipStream_t s, double *out) {
 int domain_energy(DomainState &d, hipStream_t s, const double *U, double rho_ref, double *out) {
     const Layout &L = d.L;
     const bool dev = d.cfg.dtype != LBM_FP64;
-    EnergyArgs ea{d.buf[d.cur], L.n, (int)d.cfg.nx, L.ps, L.rs, d.relax.rho0, rho_ref, {0.0, 0.0, 0.0},
-                  d.partials};
+    EnergyArgs ea{d.buf[d.cur], L.n,     (int)d.cfg.nx,   L.ps,       L.rs,
+                  d.relax.rho0, rho_ref, {0.0, 0.0, 0.0}, d.partials, reinterpret_cast<unsigned *>(d.flag + 1),
+                  out};
     for (int a = 0; a < L.dim; ++a)
         ea.U[a] = U ? U[a] : 0.0;
     void (*fn)(EnergyArgs) = L.dim == 1   ? (dev ? k_energy<1, true> : k_energy<1, false>)
                              : L.dim == 2 ? (dev ? k_energy<2, true> : k_energy<2, false>)
                                           : (dev ? k_energy<3, true> : k_energy<3, false>);
     hipLaunchKernelGGL(fn, dim3((unsigned)L.red_blocks), dim3(kReduceThreads), 0, s, ea);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kReduceThreads), 0, s, (const double *)d.partials,
-                       L.red_blocks, out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return hip_fail(e, "energy launch");
@@ -666,6 +668,7 @@ struct lbm_handle {
     hipGraph_t graph[2] = {nullptr, nullptr};  // by the buffer holding the state at the start
     hipGraphExec_t exec[2] = {nullptr, nullptr};
     bool graphs_off = false;                   // a graph call failed once: plain launches only
+    double *host = nullptr;                    // pinned: results of lbm_moments (NULL: none could be had)
 };
 
 // Pack: plane 0's populations with c_z = -1 into `lower`, plane nz - 1's with
@@ -778,6 +781,10 @@ int lbm_create_tuned(const lbm_config *cfg, const lbm_tuning *tuning, void *work
         delete h;
         set_error("initial state has a node with rho <= 0 or |u_alpha| >= 1");
         return LBM_EDOMAIN;
+    }
+    if (hipHostMalloc(reinterpret_cast<void **>(&h->host), kHostBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        h->host = nullptr;
     }
     // capture the step graphs now, so that no later call pays for it
     if (!L.zhalo) {
@@ -1029,7 +1036,7 @@ int lbm_moments(lbm_handle *h, double *rho, double *u, lbm_diag *diag) {
         set_error("NULL handle");
         return LBM_EINVAL;
     }
-    return domain_moments(h->d, h->stream, rho, u, diag);
+    return domain_moments(h->d, h->stream, rho, u, diag, h->host);
 }
 
 int lbm_energy(lbm_handle *h, const double *U, double rho_ref, double *out) {
@@ -1203,6 +1210,8 @@ int lbm_destroy(lbm_handle *h) {
     }
     if (h->capture)
         keep(hipStreamDestroy(h->capture));
+    if (h->host)
+        keep(hipHostFree(h->host));
     delete h;
     if (e != hipSuccess)
         return hip_fail(e, "destroy synchronise");

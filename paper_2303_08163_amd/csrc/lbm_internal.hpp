@@ -84,7 +84,9 @@ int domain_bind_and_init(DomainState &d, const lbm_config *cfg, const Layout &L,
                          const double *rho, const double *u, hipStream_t s);
 // Synchronise the stream and return the domain flag (0/1) in *flag.
 int domain_read_flag(const DomainState &d, hipStream_t s, int *flag);
-int domain_moments(DomainState &d, hipStream_t s, double *rho, double *u, lbm_diag *diag);
+// host: kHostBytes of pinned memory for the result, or NULL.  Synchronises s.
+constexpr size_t kHostBytes = 256;
+int domain_moments(DomainState &d, hipStream_t s, double *rho, double *u, lbm_diag *diag, double *host);
 int domain_export(DomainState &d, hipStream_t s, double *out);
 // Enqueue the acoustic energy about (rho_ref, U) into the device double *out.
 int domain_energy(DomainState &d, hipStream_t s, const double *U, double rho_ref, double *out);

@@ -251,7 +251,7 @@ struct lbm_pool {
     int64_t ep_seq[kEpochRing] = {};
     int64_t epoch = 0;
     std::vector<int64_t> run_epoch;  // epoch of run r at index r - 1
-    char *gather_host = nullptr;  // pinned: flag pointers, then flag values
+    char *gather_host = nullptr;  // pinned: flag pointers, then flag values, then a read's diagnostics
     char *gather_dev = nullptr;
     int cu_count = 0;
     int64_t runs = 0, launches = 0;
@@ -457,7 +457,8 @@ int lbm_pool_create(int32_t max_slots, const lbm_pool_tuning *tuning, void *aren
     for (int k = 0; k < kEpochRing && e == hipSuccess; ++k)
         e = hipEventCreateWithFlags(&p->ep_ev[k], hipEventDisableTiming);
     if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&p->gather_host), gather_bytes(max_slots), hipHostMallocDefault);
+        e = hipHostMalloc(reinterpret_cast<void **>(&p->gather_host), gather_bytes(max_slots) + kHostBytes,
+                          hipHostMallocDefault);
     if (e == hipSuccess)
         e = hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking);
     if (e == hipSuccess) {
@@ -1047,7 +1048,7 @@ int lbm_pool_moments(lbm_pool *p, int32_t slot, double *rho, double *u, lbm_diag
     rc = read_stream(p, s, &st);
     if (rc != LBM_OK)
         return rc;
-    return domain_moments(s.d, st, rho, u, diag);
+    return domain_moments(s.d, st, rho, u, diag, reinterpret_cast<double *>(p->gather_host + gather_bytes(p->max_slots)));
 }
 
 int lbm_pool_get_populations(lbm_pool *p, int32_t slot, double *out) {
