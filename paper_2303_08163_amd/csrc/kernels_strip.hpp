@@ -1,5 +1,6 @@
 // kernels_strip.hpp -- several LBGK steps per launch with the intermediate
-// states in registers: K steps on D2Q9 (k_strip2) and on D1Q3 (k_strip1).
+// states in registers: K steps on D2Q9 (k_strip2, and k_block2 for small
+// domains) and on D1Q3 (k_strip1).
 //
 // A wavefront owns a strip of columns.  Its 64 lanes hold 64 NC consecutive
 // columns (NC per lane), of which the outer H on each side are halo: a
@@ -248,6 +249,127 @@ __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(W
             break;
     }
     raise_flag(a.flag, bad_any && mine);
+}
+
+// D2Q9 block: K steps of a small block, for domains too small to fill the chip
+// with strips.  A workgroup holds 64 columns (one per lane) of RPT rows per
+// wavefront, every row at once: the rows' x neighbours come by lane moves, the y
+// neighbours inside a wavefront from its registers and between wavefronts
+// through LDS (three populations of the first and of the last row, two buffers
+// used in turn, one barrier a step).  Step 1 pulls from HBM, so the block has
+// K - 1 halo columns and rows on each side and 64 - 2 (K - 1) own columns.
+//
+// Bound: the gap between launches (2.6 us) and the latency of a step's chain of
+// FP64 operations, about 1.2 us per four steps for each row a SIMD holds; one
+// step per launch paid the gap every step (us per step, before / after: 64^2
+// FP64 2.84 / 1.20, 200 x 150 3.03 / 1.46, 300^2 4.50 / 1.86, 500 x 333 FP32 with the
+// correction 4.23 / 2.61).
+struct BlockArgs {
+    const void *src;  // f*(t), row-interleaved layout
+    void *dst;        // f*(t + K)
+    int nx, ny;
+    int K;
+    int own_x, own_y;  // own columns and rows per workgroup
+    int tiles_x;
+    int64_t ps, rs;
+    Relax relax;
+    int *flag;
+};
+
+// most wavefronts of a workgroup: 128 registers a lane with one row, 168 with two
+__host__ __device__ constexpr int block_waves(int rpt) { return rpt == 1 ? 16 : 12; }
+
+template <int DT, bool CORR, int EQ, int RPT>
+__global__ __launch_bounds__(64 * block_waves(RPT)) void k_block2(BlockArgs a) {
+    using T = store_t<DT>;
+    constexpr int NW = block_waves(RPT);
+    __shared__ T edge[2][NW][6][64];
+    typedef const __attribute__((address_space(1))) char *Gin;
+    typedef __attribute__((address_space(1))) char *Gout;
+    const Gin src = (Gin)a.src;
+    const Gout dst = (Gout)a.dst;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = (int)blockDim.x >> 6;
+    const int lane = (int)threadIdx.x & 63;
+    const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int nx = a.nx, ny = a.ny, h = a.K - 1;
+    const int x0 = (tile % a.tiles_x) * a.own_x, y0 = (tile / a.tiles_x) * a.own_y;
+    int x = (x0 - h + lane) % nx;
+    x = x < 0 ? x + nx : x;
+    const uint32_t xb[3] = {(uint32_t)(x + 1 == nx ? 0 : x + 1) * (uint32_t)sizeof(T), (uint32_t)x * (uint32_t)sizeof(T),
+                            (uint32_t)(x == 0 ? nx - 1 : x - 1) * (uint32_t)sizeof(T)};  // x - c_x
+    const int64_t psb = a.ps * (int64_t)sizeof(T), rsb = a.rs * (int64_t)sizeof(T);
+    const int r0 = wave * RPT - h;  // the wavefront's first row within the own rows
+    T f[RPT][9];
+    {
+        int y = (y0 + r0) % ny;
+        y = y < 0 ? y + ny : y;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const int yp = y + 1 == ny ? 0 : y + 1, ym = y == 0 ? ny - 1 : y - 1;
+            const Gin base[3] = {src + yp * rsb, src + y * rsb, src + ym * rsb};
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                f[j][i] = *(const __attribute__((address_space(1))) T *)(base[i / 3] + i * psb + xb[i % 3]);
+            y = yp;
+        }
+    }
+    // own rows and columns; the domain flag is taken from them at every step
+    const bool own_col = lane >= h && lane < h + a.own_x && x0 + lane - h < nx;
+    bool bad = false;
+    auto relax_rows = [&] {
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const bool b = collide_dt<2, DT, CORR, EQ>(f[j], a.relax);
+            const bool own_row = r0 + j >= 0 && r0 + j < a.own_y && y0 + r0 + j < ny;  // uniform
+            bad |= b && own_row;
+        }
+    };
+    relax_rows();
+    for (int k = 1; k < a.K; ++k) {
+        T(*e)[6][64] = edge[k & 1];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            e[wave][q][lane] = f[0][q];                // to the row below the first
+            e[wave][3 + q][lane] = f[RPT - 1][6 + q];  // to the row above the last
+        }
+        __syncthreads();
+        // (the block's outermost rows have no neighbour there: halo rows no later step uses)
+        const int up = wave + 1 < waves ? wave + 1 : wave, down = wave > 0 ? wave - 1 : wave;
+        T in[2][3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            in[0][q] = e[up][q][lane];
+            in[1][q] = e[down][3 + q][lane];
+        }
+        // row j pulls c_y = -1 from row j + 1 and c_y = +1 from row j - 1
+        T g[RPT][9];
+#pragma unroll
+        for (int j = 0; j < RPT; ++j)
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                const T v = i < 3 ? (j + 1 < RPT ? f[j + 1 < RPT ? j + 1 : j][i] : in[0][i])
+                                  : (i < 6 ? f[j][i] : (j > 0 ? f[j > 0 ? j - 1 : j][i] : in[1][i - 6]));
+                g[j][i] = i % 3 == 1 ? v : (i % 3 == 2 ? lane_move<false>(v) : lane_move<true>(v));
+            }
+#pragma unroll
+        for (int j = 0; j < RPT; ++j)
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                f[j][i] = g[j][i];
+        relax_rows();
+    }
+    raise_flag(a.flag, bad && own_col);
+    if (!own_col)
+        return;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        if (r0 + j >= 0 && r0 + j < a.own_y && y0 + r0 + j < ny) {  // uniform
+            const Gout row = dst + (int64_t)(y0 + r0 + j) * rsb;
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                *(__attribute__((address_space(1))) T *)(row + i * psb + xb[1]) = f[j][i];
+        }
+    }
 }
 
 // One D1Q3 wavefront: K steps (1 .. h) of the strip's own columns.  h and tx are

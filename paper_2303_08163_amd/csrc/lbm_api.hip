@@ -337,13 +337,13 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
     }
     L.buf_bytes = (size_t)elems * L.elem;
     // runs left to the library take more steps per launch than time_block where they pay
-    L.deep = !automatic ? 0 : L.dim == 1 ? (L.tblock > 1 ? strip1_steps(cfg->nx) : 0)
-                          : L.dim == 2   ? strip2_steps(cfg, L)
-                                         : (sweep3_takes(cfg, L) ? 2 : 0);
-    if (L.deep && L.dim == 2) {
-        L.strip_rows[0] = strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 4);
-        L.strip_rows[1] = L.deep == 6 ? strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 6) : 0;
-    }
+    L.deep = 0;
+    if (automatic && L.dim == 1 && L.tblock > 1)
+        L.deep = strip1_steps(cfg->nx);
+    else if (automatic && L.dim == 2)
+        plan2(cfg, L);
+    else if (automatic && sweep3_takes(cfg, L))
+        L.deep = 2;
     if (L.deep && L.dim == 3)
         L.sweep3 = sweep3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem);
     L.red_blocks = (int)std::min<int64_t>(1024, (L.n + kReduceThreads - 1) / kReduceThreads);
@@ -825,15 +825,16 @@ static int enqueue_deep(lbm_handle *h, int cur, int K, hipStream_t s) {
                d.L.ps, d.L.rs, d.relax, d.flag, 0};
     const bool corr = d.cfg.bulk_correction != 0;
     return d.L.dim == 1   ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
+           : d.L.block2.rpt ? launch_block2(d.L, a, d.cfg.dtype, corr, K, s)
            : d.L.dim == 2 ? launch_strip2(d.L, a, d.cfg.dtype, corr, K, s)
                           : launch_sweep3(d.L, a, d.cfg.dtype, corr, s);
 }
 
-// Steps of the next launch of a run with n steps left.  D1Q3 strips take any
-// number; D2Q9 strips 4, or 6 and 4 (FP64), so that a count that leaves 2 or 3
+// Steps of the next launch of a run with n steps left.  D1Q3 strips and D2Q9
+// blocks take any number; D2Q9 strips 4, or 6 and 4 (FP64), so that a count that leaves 2 or 3
 // of the sixes takes two fours instead; D3Q27 sweeps 2.
 static int next_steps(const Layout &L, int64_t n) {
-    if (L.deep && L.dim == 1)
+    if (L.deep && (L.dim == 1 || L.block2.rpt))
         return (int)std::min<int64_t>(n, L.deep);
     if (L.deep == 6 && n >= 6 && !(n >= 8 && (n % 6 == 2 || n % 6 == 3)))
         return 6;

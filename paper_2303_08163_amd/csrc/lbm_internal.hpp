@@ -17,6 +17,12 @@ struct Sweep3Geom {
     int w, rows, planes;
 };
 
+// Tiling of a small D2Q9 domain's blocks (strip.hip): rows per wavefront (0: the
+// domain takes no blocks), wavefronts, own columns and rows per workgroup.
+struct Block2Geom {
+    int rpt, waves, own_x, own_y, tiles_x, tiles_y;
+};
+
 // Workspace layout of one domain (all offsets in bytes, 256-byte aligned).
 struct Layout {
     int dim, q;
@@ -33,6 +39,7 @@ struct Layout {
     int t2_tx, t2_rows;  // multi-step kernels: owned columns (nodes) and rows per workgroup
     int deep;          // steps of the longest launch of a run (strips, sweeps; 0: tblock)
     int strip_rows[2]; // D2Q9 strips: own rows per wavefront with 4 and with 6 steps
+    Block2Geom block2; // D2Q9 blocks
     Sweep3Geom sweep3; // D3Q27 sweeps
     bool zhalo;        // z-slab: each buffer holds halo planes -1 and nz around the nz planes
     int64_t plane;     // elements of one plane (rows layout: ny * rs)
@@ -62,15 +69,16 @@ int launch_step(const Layout &L, const StepArgs &args, int dtype, bool corr, hip
                 const HaloArgs *halo);
 int launch_step2(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
 
-// Register-strip launches (strip.hip).
-constexpr int64_t kStrip2Nodes = 128 * 1024;  // D2Q9 domains from here on
-constexpr int64_t kStrip1Wide = 1 << 22;      // D1Q3 rows with many columns per lane
-int strip2_steps(const lbm_config *cfg, const Layout &L);
-int strip2_rows(int64_t nx, int64_t ny, int dtype, int K);
+// Launches with the intermediate states in registers (strip.hip).
+constexpr int kBlock2Steps = 4;           // steps per launch of D2Q9 blocks
+constexpr int64_t kStrip1Wide = 1 << 22;  // D1Q3 rows with many columns per lane
+void plan2(const lbm_config *cfg, Layout &L);
 int strip1_steps(int64_t nx);
 int strip1_cols(int64_t nx, int dtype, int K);
 int launch_strip1(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
 int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
+
+int launch_block2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
 
 // Two-step D3Q27 sweeps (sweep3.hip).
 constexpr size_t kSweep3Bytes = (size_t)96 << 20;  // both population buffers from here on

@@ -10,32 +10,20 @@
 
 namespace lbm {
 
+constexpr double kLaunchUs = 2.6;  // from one launch of a small kernel to the next
+
 // Registers of k_strip2 and so the wavefronts a SIMD holds: FP32 storage takes
 // 4 steps in at most 168 registers (three wavefronts), FP64 4 steps (three)
 // or 6 (240 registers, two).
 constexpr int strip2_occupancy(int dtype, int K) { return dtype == kF64 && K == 6 ? 2 : 3; }
 
-// D2Q9: steps per launch of the longest strip launch, 0 for none.  FP32
-// storage is bound by the FP64 arithmetic at 4 steps already (4096^2, us per
-// step: 3 steps 101.5, 4 steps 89.6, 6 steps 98.4 with one wavefront per SIMD
-// less); FP64 storage by HBM until 6 (4 steps 131.8, 5 112.6, 6 96.6, 8 118.6
-// with one wavefront per SIMD).
-int strip2_steps(const lbm_config *cfg, const Layout &L) {
-    if (L.dim != 2 || L.layout != LBM_LAYOUT_ROWS || (cfg->dtype != LBM_FP64 && cfg->dtype != LBM_FP32_DEV))
-        return 0;
-    // byte offsets inside a row are 32-bit; below 64 nodes most columns of a wavefront are copies
-    if (cfg->nx < 64 || cfg->nx > (1 << 28) || L.n < kStrip2Nodes)
-        return 0;
-    return cfg->dtype == LBM_FP64 ? 6 : 4;
-}
-
 // Own rows per wavefront of k_strip2: the row chunks with the least estimated
-// time.  A sweep
-// over R own rows takes R + 2 K - 2 iterations, and an iteration with w
-// wavefronts on every SIMD about 0.7 + w units (1024^2, 4 steps: 1.32 us with
-// one, 2.09 with two, 2.86 with three; one wavefront alone waits for its own
-// results).  More chunks than fit at once run in rounds.
-int strip2_rows(int64_t nx, int64_t ny, int dtype, int K) {
+// time, and that time in us per launch.  A sweep over R own rows takes
+// R + 2 K - 2 iterations, and an iteration with w wavefronts on every SIMD about
+// 0.54 + 0.77 w us (1024^2, 4 steps: 1.32 us with one, 2.09 with two, 2.86 with
+// three; one wavefront alone waits for its own results).  More chunks than fit
+// at once run in rounds.
+static int strip2_rows(int64_t nx, int64_t ny, int dtype, int K, double *us) {
     const int64_t strips = (nx + 63 - 2 * K) / (64 - 2 * K);
     const int occ = strip2_occupancy(dtype, K);
     int64_t best_c = 1;
@@ -43,14 +31,72 @@ int strip2_rows(int64_t nx, int64_t ny, int dtype, int K) {
     for (int64_t c = 1; c <= std::max<int64_t>(1, ny / 4); c += 1 + c / 64) {
         const int64_t R = (ny + c - 1) / c, waves = strips * ((ny + R - 1) / R);
         const int64_t slots = 1024 * occ, full = waves / slots, rest = waves % slots;
-        const double cost =
-            (double)(R + 2 * K - 2) * ((double)full * (0.7 + occ) + (rest ? 0.7 + (double)((rest + 1023) / 1024) : 0.0));
+        const double cost = (double)(R + 2 * K - 2) * ((double)full * (0.54 + 0.77 * occ) +
+                                                       (rest ? 0.54 + 0.77 * (double)((rest + 1023) / 1024) : 0.0));
         if (best < 0.0 || cost < best) {
             best = cost;
             best_c = c;
         }
     }
+    *us = kLaunchUs + best;
     return (int)((ny + best_c - 1) / best_c);
+}
+
+// Tiling of k_block2 for four steps per launch: rows per wavefront and wavefronts
+// with the least estimated time, and that time in us per launch.  A compute
+// unit that holds q rows of wavefronts on each SIMD takes about 1.25 q us for the
+// four steps (64^2, one wavefront row each, 8 wavefronts: 4.8 us with the launch;
+// 12: 6.1; 300^2 16: 7.7; two rows each, 8: 7.9; 512^2, two such workgroups per
+// compute unit: 13.0).
+static Block2Geom block2_geom(int64_t nx, int64_t ny, double *us) {
+    Block2Geom g{};
+    constexpr int K = kBlock2Steps, own = 64 - 2 * (K - 1);
+    const int64_t tiles_x = (nx + own - 1) / own;
+    *us = -1.0;
+    for (int rpt : {1, 2})
+        for (int waves = 4; waves <= block_waves(rpt); ++waves) {
+            const int rows = waves * rpt - 2 * (K - 1);
+            if (rows < 1)
+                continue;
+            const int64_t tiles_y = (ny + rows - 1) / rows, wgs = tiles_x * tiles_y;
+            const double t =
+                kLaunchUs + 1.25 * (double)((wgs + 255) / 256) * (double)((waves + 3) / 4 * rpt);
+            if (*us < 0.0 || t < *us - 1e-9 || (t < *us + 1e-9 && wgs < (int64_t)g.tiles_x * g.tiles_y)) {
+                *us = t;
+                g.rpt = rpt;
+                g.waves = waves;
+                g.tiles_x = (int)tiles_x;
+                g.tiles_y = (int)tiles_y;
+            }
+        }
+    g.own_x = (int)((nx + g.tiles_x - 1) / g.tiles_x);
+    g.own_y = (int)((ny + g.tiles_y - 1) / g.tiles_y);
+    return g;
+}
+
+// Which form the runs of a D2Q9 domain take: strips of 4 steps per launch (FP32)
+// or 6 and 4 (FP64), blocks of 4, by the estimated time per step, or neither.
+// FP32 strips are bound by the FP64 arithmetic at 4 steps already (4096^2, us
+// per step: 3 steps 101.5, 4 steps 89.6, 6 steps 98.4 with one wavefront per
+// SIMD less); FP64 by HBM until 6 (4 steps 131.8, 5 112.6, 6 96.6, 8 118.6 with
+// one wavefront per SIMD).  Blocks win below about 600^2 (us per step, FP64 blocks /
+// strips: 512^2 3.3 / 4.2, 700 x 600 5.0 / 5.1, 1024^2 9.2 / 8.3).
+void plan2(const lbm_config *cfg, Layout &L) {
+    if (L.dim != 2 || L.layout != LBM_LAYOUT_ROWS || (cfg->dtype != LBM_FP64 && cfg->dtype != LBM_FP32_DEV))
+        return;
+    if (cfg->nx > (1 << 28))  // byte offsets inside a row are 32-bit
+        return;
+    double us4, us6 = 0.0, usb;
+    const bool six = cfg->dtype == LBM_FP64;
+    L.strip_rows[0] = strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 4, &us4);
+    L.strip_rows[1] = six ? strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 6, &us6) : 0;
+    const Block2Geom g = block2_geom(cfg->nx, cfg->ny, &usb);
+    if (L.tblock == 1 && usb / kBlock2Steps < (six ? us6 / 6 : us4 / 4)) {
+        L.block2 = g;
+        L.deep = kBlock2Steps;
+    } else {
+        L.deep = six ? 6 : 4;
+    }
 }
 
 template <int DT, int K, int EQ, bool NT>
@@ -96,6 +142,32 @@ int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return hip_fail(e, "strip launch");
+    return LBM_OK;
+}
+
+template <int DT, int EQ, int RPT>
+static void (*block2_corr(bool corr))(BlockArgs) {
+    return corr ? k_block2<DT, true, EQ, RPT> : k_block2<DT, false, EQ, RPT>;
+}
+template <int DT, int RPT>
+static void (*block2_kernel(int eq, bool corr))(BlockArgs) {
+    return eq == LBM_EQ_POLY2     ? block2_corr<DT, kEqPoly2, RPT>(corr)
+           : eq == LBM_EQ_PRODUCT ? block2_corr<DT, kEqProduct, RPT>(corr)
+                                  : block2_corr<DT, kEqEntropic, RPT>(corr);
+}
+
+// K <= kBlock2Steps steps (fewer leave more halo than they need).
+int launch_block2(const Layout &L, const StepArgs &s, int dtype, bool corr, int K, hipStream_t stream) {
+    const Block2Geom &g = L.block2;
+    const BlockArgs a{s.src, s.dst, s.nx, s.ny, K, g.own_x, g.own_y, g.tiles_x, L.ps, L.rs, s.relax, s.flag};
+    void (*fn)(BlockArgs) = dtype == kF64 ? (g.rpt == 1 ? block2_kernel<kF64, 1>(L.eq, corr)
+                                                        : block2_kernel<kF64, 2>(L.eq, corr))
+                                          : (g.rpt == 1 ? block2_kernel<kDevF64, 1>(L.eq, corr)
+                                                        : block2_kernel<kDevF64, 2>(L.eq, corr));
+    hipLaunchKernelGGL(fn, dim3((unsigned)((int64_t)g.tiles_x * g.tiles_y)), dim3(64u * (unsigned)g.waves), 0, stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return hip_fail(e, "block launch");
     return LBM_OK;
 }
 

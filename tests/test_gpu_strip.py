@@ -1,6 +1,5 @@
-"""Register-strip launches (K steps per launch, the intermediate states in
-registers): the default of D1Q3 rows and of D2Q9 domains of at least 2^17
-nodes.  Every run is bitwise the one-step-per-launch run (time_block = 1): the
+"""Launches of K steps with the intermediate states in registers, the default of
+D1Q3 rows and D2Q9 domains: strips, and blocks for small D2Q9 domains.  Every run is bitwise the one-step-per-launch run (time_block = 1): the
 same per-node code, and float storage rounds after every step in both."""
 import numpy as np
 import pytest
@@ -32,21 +31,21 @@ def _compare(shape, dtype, corr, eq, chunks, seed, umax=0.1):
 
 
 D2_CASES = [  # (ny, nx), dtype, correction, equilibrium, step chunks
-    ((512, 256), "fp32_dev", False, "entropic", (4, 5, 6, 7, 100)),
-    ((512, 256), "fp64", True, "entropic", (6, 7, 8, 9, 10, 11, 100)),
+    ((2500, 512), "fp32_dev", False, "entropic", (4, 5, 6, 7, 100)),
+    ((2500, 512), "fp64", True, "entropic", (6, 7, 8, 9, 10, 11, 100)),
     # widths one off a multiple of the own columns (56 and 52), odd heights
-    ((393, 337), "fp32_dev", True, "entropic", (4, 67)),
-    ((397, 335), "fp64", False, "entropic", (6, 71)),
-    ((403, 365), "fp64", True, "product", (12, 4)),
-    ((411, 363), "fp64", False, "poly2", (13,)),
-    ((401, 391), "fp32_dev", False, "poly2", (9,)),
-    ((399, 393), "fp32_dev", True, "product", (8,)),
+    ((3001, 337), "fp32_dev", True, "entropic", (4, 67)),
+    ((1801, 1093), "fp64", False, "entropic", (6, 71)),
+    ((1703, 1091), "fp64", True, "product", (12, 4)),
+    ((2011, 989), "fp64", False, "poly2", (13,)),
+    ((1201, 1009), "fp32_dev", False, "poly2", (9,)),
+    ((1999, 785), "fp32_dev", True, "product", (8,)),
     # the narrowest rows, and fewer rows than a sweep's halo (wrapped several times)
-    ((2049, 64), "fp32_dev", False, "entropic", (12, 3)),
-    ((2017, 65), "fp64", False, "entropic", (14,)),
-    ((1, 131072), "fp64", True, "entropic", (14, 3)),
-    ((2, 65537), "fp32_dev", True, "entropic", (8, 5)),
-    ((5, 30001), "fp64", False, "entropic", (18,)),
+    ((30049, 64), "fp32_dev", False, "entropic", (12, 3)),
+    ((30017, 65), "fp64", False, "entropic", (14,)),
+    ((1, 1048576), "fp64", True, "entropic", (14, 3)),
+    ((2, 655361), "fp32_dev", True, "entropic", (8, 5)),
+    ((5, 300001), "fp64", False, "entropic", (18,)),
     # non-temporal stores (the two buffers exceed the last-level cache)
     ((2050, 2049), "fp32_dev", False, "entropic", (10,)),
     ((1500, 1501), "fp64", True, "entropic", (12,)),
@@ -57,6 +56,34 @@ D2_CASES = [  # (ny, nx), dtype, correction, equilibrium, step chunks
 def test_d2q9_strips_equal_one_step_bitwise(case):
     shape, dtype, corr, eq, chunks = D2_CASES[case]
     _compare(shape, dtype, corr, eq, chunks, seed=300 + case)
+
+
+BLOCK_CASES = [  # (ny, nx), dtype, correction, equilibrium, step chunks
+    ((64, 64), "fp64", False, "entropic", (1, 2, 3, 4, 5, 100)),
+    ((64, 64), "fp32_dev", True, "entropic", (3, 7, 64)),
+    # extents one off the own columns (58) and rows, and of one or two workgroups
+    ((2, 58), "fp64", True, "entropic", (4, 3)),
+    ((3, 59), "fp32_dev", False, "product", (6,)),
+    ((10, 57), "fp64", False, "poly2", (9,)),
+    ((11, 116), "fp32_dev", True, "poly2", (66,)),
+    ((61, 117), "fp64", True, "product", (13,)),
+    # fewer columns or rows than the halo (wrapped onto the domain itself)
+    ((1, 1), "fp64", False, "entropic", (6,)),
+    ((1, 70), "fp32_dev", False, "entropic", (4, 2)),
+    ((70, 1), "fp64", True, "entropic", (5,)),
+    ((5, 3), "fp32_dev", True, "entropic", (8, 64)),
+    ((300, 17), "fp64", False, "entropic", (10,)),
+    # two rows per wavefront, several workgroups per compute unit
+    ((333, 500), "fp32_dev", True, "entropic", (6, 64)),
+    ((300, 300), "fp64", False, "entropic", (7,)),
+    ((512, 509), "fp64", True, "entropic", (11,)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(BLOCK_CASES)))
+def test_d2q9_blocks_equal_one_step_bitwise(case):
+    shape, dtype, corr, eq, chunks = BLOCK_CASES[case]
+    _compare(shape, dtype, corr, eq, chunks, seed=600 + case)
 
 
 D1_CASES = [  # nx, dtype, correction, equilibrium, step chunks
@@ -82,7 +109,7 @@ def test_d1q3_strips_equal_one_step_bitwise(case):
     _compare((nx,), dtype, corr, eq, chunks, seed=400 + case)
 
 
-@pytest.mark.parametrize("shape,dtype", [((300, 500), "fp64"), ((400, 400), "fp32_dev"), ((3000,), "fp64")])
+@pytest.mark.parametrize("shape,dtype", [((64, 64), "fp64"), ((1100, 900), "fp64"), ((400, 400), "fp32_dev"), ((3000,), "fp64")])
 def test_strips_raise_the_domain_flag_as_one_step(shape, dtype):
     """A state about to leave the domain raises the flag in the same call, and
     the halo columns' and rows' unused values raise none in a healthy one."""
