@@ -88,11 +88,21 @@ struct StripVec<T, 1> {
 // row b just computed, step j + 1 at row b - 1 pulls the populations with
 // c_y = -1 from row b, c_y = 0 from row b - 1 and c_y = +1 from row b - 2, so a
 // level keeps three populations of one row and three of two rows, nine values a
-// column, in registers.  Step j + 1 starts at s = 2 j.
-template <int DT, bool CORR, int EQ, int K, int NC, bool NT, int WPE>
+// column, in registers.  Step j + 1 starts at s = 2 j.  Step 1 loads each
+// population at its own source column, so K - 1 halo columns do.
+//
+// Bound: the FP64 arithmetic of the collisions with float storage (4096^2, four
+// steps: 137 VALU instructions per node update and 1.2 times the nodes, at 80 %
+// of the issue rate with three wavefronts per SIMD), arithmetic and HBM alike
+// with double (six steps).  us per step at 4096^2, against the two-step sweep
+// through LDS: FP32 117 -> 88, FP64 212 -> 95.  Two columns per lane spill
+// (543 us per launch against 358); more than 168 / 256 registers a lane would
+// be needed for five (FP32) or eight (FP64) steps at the same occupancy.  A
+// barrier per row that keeps a workgroup's strips together gave 2 % on 4096^2 FP32
+// and cost up to 10 % where a SIMD holds one wavefront (1024^2 FP64).
+template <int DT, bool CORR, int EQ, int K, int WPE>
 __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(WPE))) void k_strip2(StripArgs a) {
     using T = store_t<DT>;
-    using V = typename StripVec<T, NC>::type;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int lane = (int)threadIdx.x & 63;
     const int w = xcd_tile((int)blockIdx.x, (int)gridDim.x) * (kStripThreads / 64) + wave;
@@ -108,137 +118,79 @@ __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(W
     const int nx = a.nx, ny = a.ny;
     const int x0 = strip * a.tx;
     const int y0 = chunk * a.rows, R = min(a.rows, ny - y0);
-    // columns of this lane, wrapped; a strip whose loaded columns lie inside the
-    // row moves them as one vector
-    const bool inside = x0 >= a.h && x0 - a.h + 64 * NC <= nx;
-    uint32_t xb[NC];
-    {
-        int x = (x0 - a.h + lane * NC) % nx;
-        x = x < 0 ? x + nx : x;
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            xb[k] = (uint32_t)(x * (int)sizeof(T));
-            x = x + 1 == nx ? 0 : x + 1;
-        }
-    }
-    const int own = lane * NC - a.h;  // first column of the lane within the strip's own
-    const bool mine = own >= 0 && own < a.tx;
-
-    auto load_run = [&](Gin base, T (&f)[NC]) {
-        if constexpr (NC == 1) {
-            f[0] = *(const __attribute__((address_space(1))) T *)(base + xb[0]);
-        } else if (inside) {
-            const V v = *(const __attribute__((address_space(1))) V *)(base + xb[0]);
-#pragma unroll
-            for (int k = 0; k < NC; ++k)
-                f[k] = v[k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < NC; ++k)
-                f[k] = *(const __attribute__((address_space(1))) T *)(base + xb[k]);
-        }
-    };
+    int x = (x0 - a.h + lane) % nx;  // this lane's column, wrapped
+    x = x < 0 ? x + nx : x;
+    // byte offsets of its source columns x - c_x
+    uint32_t xb[3] = {(uint32_t)(x + 1 == nx ? 0 : x + 1) * (uint32_t)sizeof(T), (uint32_t)x * (uint32_t)sizeof(T),
+                      (uint32_t)(x == 0 ? nx - 1 : x - 1) * (uint32_t)sizeof(T)};
+    const int own = lane - a.h;
+    const bool mine = own >= 0 && own < a.tx && x0 + own < nx;
     const int64_t psb = a.ps * (int64_t)sizeof(T), rsb = a.rs * (int64_t)sizeof(T);  // strides in bytes
+
     // the nine runs of a step-1 row: c_y = -1 from the row above, 0, +1 from below
     int yl;  // wrapped row of the next load's c_y = 0 runs
-    // (an empty asm on the lane's byte offset, here and at the stores: its widening
-    // to 64 bits then stays beside the access, which so takes a scalar base and a
-    // 32-bit vector offset instead of a 64-bit vector address of its own)
-    auto load_row = [&](T (&f)[9][NC]) {
-#pragma unroll
-        for (int k = 0; k < NC; ++k)
-            asm("" : "+v"(xb[k]));
+    // (an empty asm on the lane's byte offsets, here and at the stores: their
+    // widening to 64 bits then stays beside the access, which so takes a scalar base
+    // and a 32-bit vector offset instead of a 64-bit vector address of its own)
+    auto load_row = [&](T (&f)[9]) {
         const int yp = yl + 1 == ny ? 0 : yl + 1, ym = yl == 0 ? ny - 1 : yl - 1;
-        const int64_t off[3] = {(int64_t)yp * rsb, (int64_t)yl * rsb, (int64_t)ym * rsb};
+        const Gin base[3] = {src + (int64_t)yp * rsb, src + (int64_t)yl * rsb, src + (int64_t)ym * rsb};
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            asm("" : "+v"(xb[k]));
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            load_run(src + (off[i / 3] + i * psb), f[i]);
+            f[i] = *(const __attribute__((address_space(1))) T *)(base[i / 3] + i * psb + xb[i % 3]);
         yl = yp;
     };
 
     const int S = R + 2 * K - 2;  // sweep iterations
-    T A[K - 1][3][NC];            // level j's last row, c_y = 0
-    T B[K - 1][2][3][NC];         // level j's last two rows, c_y = +1, by iteration parity
+    T A[K - 1][3];                // level j's last row, c_y = 0
+    T B[K - 1][2][3];             // level j's last two rows, c_y = +1, by iteration parity
     bool bad_any = false;
-
-    auto relax_row = [&](const T (&g)[9][NC], T (&o)[9][NC]) {
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            T f[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i)
-                f[i] = g[i][k];
-            bad_any |= collide_dt<2, DT, CORR, EQ>(f, a.relax);
-#pragma unroll
-            for (int i = 0; i < 9; ++i)
-                o[i][k] = f[i];
-        }
-    };
     int ys = y0;  // next row to store
-    auto iteration = [&](T (&in)[9][NC], int s, auto pp) {
+    auto iteration = [&](T (&in)[9], int s, auto pp) {
         constexpr int P = decltype(pp)::value;
-        T g[9][NC], o[9][NC];
+        T o[9];
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            pull_columns<T, NC>(in[i], i % 3, g[i]);
-        relax_row(g, o);
+            o[i] = in[i];
+        bad_any |= collide_dt<2, DT, CORR, EQ>(o, a.relax);
         if (s + 1 < S)  // the next row's loads, in flight during the steps below
             load_row(in);
 #pragma unroll
         for (int j = 0; j < K - 1; ++j) {
             // inputs of step j + 2 from step j + 1's rows; its last rows move on
+            T g[9];
 #pragma unroll
             for (int cx = 0; cx < 3; ++cx) {
-                pull_columns<T, NC>(o[cx], cx, g[cx]);
-                pull_columns<T, NC>(A[j][cx], cx, g[3 + cx]);
-                pull_columns<T, NC>(B[j][P][cx], cx, g[6 + cx]);
-#pragma unroll
-                for (int k = 0; k < NC; ++k) {
-                    A[j][cx][k] = o[3 + cx][k];
-                    B[j][P][cx][k] = o[6 + cx][k];
-                }
+                auto pull = [&](T v) { return cx == 1 ? v : (cx == 2 ? lane_move<false>(v) : lane_move<true>(v)); };
+                g[cx] = pull(o[cx]);
+                g[3 + cx] = pull(A[j][cx]);
+                g[6 + cx] = pull(B[j][P][cx]);
+                A[j][cx] = o[3 + cx];
+                B[j][P][cx] = o[6 + cx];
             }
             if (s < 2 * (j + 1))  // uniform: the next level has not started
                 return;
-            relax_row(g, o);
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                o[i] = g[i];
+            bad_any |= collide_dt<2, DT, CORR, EQ>(o, a.relax);
         }
         const Gout row = dst + (int64_t)ys * rsb;
         ++ys;
-        if (inside) {
-            if (mine) {
-                asm("" : "+v"(xb[0]));
+        if (mine) {
+            asm("" : "+v"(xb[1]));
 #pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    const Gout base = row + i * psb;
-                    V v;
-                    if constexpr (NC == 1)
-                        v = o[i][0];
-                    else
-#pragma unroll
-                        for (int k = 0; k < NC; ++k)
-                            v[k] = o[i][k];
-                    auto *q = (__attribute__((address_space(1))) V *)(base + xb[0]);
-                    if constexpr (NT)
-                        __builtin_nontemporal_store(v, q);
-                    else
-                        *q = v;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < NC; ++k)
-                if (mine && x0 + own + k < nx)
-#pragma unroll
-                    for (int i = 0; i < 9; ++i) {
-                        const Gout base = row + i * psb;
-                        *(__attribute__((address_space(1))) T *)(base + xb[k]) = o[i][k];
-                    }
+            for (int i = 0; i < 9; ++i)
+                *(__attribute__((address_space(1))) T *)(row + i * psb + xb[1]) = o[i];
         }
     };
 
     yl = (y0 - (K - 1)) % ny;
     yl = yl < 0 ? yl + ny : yl;
-    T in[9][NC];
+    T in[9];
     load_row(in);
     for (int s = 0;;) {
         iteration(in, s, std::integral_constant<int, 0>{});

@@ -24,7 +24,7 @@ constexpr int strip2_occupancy(int dtype, int K) { return dtype == kF64 && K == 
 // three; one wavefront alone waits for its own results).  More chunks than fit
 // at once run in rounds.
 static int strip2_rows(int64_t nx, int64_t ny, int dtype, int K, double *us) {
-    const int64_t strips = (nx + 63 - 2 * K) / (64 - 2 * K);
+    const int64_t own = 64 - 2 * (K - 1), strips = (nx + own - 1) / own;
     const int occ = strip2_occupancy(dtype, K);
     int64_t best_c = 1;
     double best = -1.0;
@@ -99,21 +99,16 @@ void plan2(const lbm_config *cfg, Layout &L) {
     }
 }
 
-template <int DT, int K, int EQ, bool NT>
+template <int DT, int K, int EQ>
 static void (*strip2_corr(bool corr))(StripArgs) {
     constexpr int W = strip2_occupancy(DT, K);
-    return corr ? k_strip2<DT, true, EQ, K, 1, NT, W> : k_strip2<DT, false, EQ, K, 1, NT, W>;
+    return corr ? k_strip2<DT, true, EQ, K, W> : k_strip2<DT, false, EQ, K, W>;
 }
 template <int DT, int K>
-static void (*strip2_kernel(int eq, bool corr, bool nt))(StripArgs) {
-    switch (eq) {
-    case LBM_EQ_POLY2:
-        return nt ? strip2_corr<DT, K, kEqPoly2, true>(corr) : strip2_corr<DT, K, kEqPoly2, false>(corr);
-    case LBM_EQ_PRODUCT:
-        return nt ? strip2_corr<DT, K, kEqProduct, true>(corr) : strip2_corr<DT, K, kEqProduct, false>(corr);
-    default:
-        return nt ? strip2_corr<DT, K, kEqEntropic, true>(corr) : strip2_corr<DT, K, kEqEntropic, false>(corr);
-    }
+static void (*strip2_kernel(int eq, bool corr))(StripArgs) {
+    return eq == LBM_EQ_POLY2     ? strip2_corr<DT, K, kEqPoly2>(corr)
+           : eq == LBM_EQ_PRODUCT ? strip2_corr<DT, K, kEqProduct>(corr)
+                                  : strip2_corr<DT, K, kEqEntropic>(corr);
 }
 
 int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int K, hipStream_t stream) {
@@ -123,8 +118,8 @@ int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int 
     a.nx = s.nx;
     a.ny = s.ny;
     a.K = K;
-    a.h = K;
-    a.tx = 64 - 2 * K;
+    a.h = K - 1;
+    a.tx = 64 - 2 * a.h;
     a.strips = (s.nx + a.tx - 1) / a.tx;
     a.rows = L.strip_rows[K == 6];
     a.chunks = (s.ny + a.rows - 1) / a.rows;
@@ -132,10 +127,9 @@ int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int 
     a.rs = L.rs;
     a.relax = s.relax;
     a.flag = s.flag;
-    const bool nt = t2_nt_stores(L.buf_bytes);
-    void (*fn)(StripArgs) = dtype == kF64 ? (K == 6 ? strip2_kernel<kF64, 6>(L.eq, corr, nt)
-                                                    : strip2_kernel<kF64, 4>(L.eq, corr, nt))
-                                          : strip2_kernel<kDevF64, 4>(L.eq, corr, nt);
+    void (*fn)(StripArgs) = dtype == kF64 ? (K == 6 ? strip2_kernel<kF64, 6>(L.eq, corr)
+                                                    : strip2_kernel<kF64, 4>(L.eq, corr))
+                                          : strip2_kernel<kDevF64, 4>(L.eq, corr);
     const int64_t waves = (int64_t)a.strips * a.chunks;
     constexpr int per_wg = kStripThreads / 64;
     hipLaunchKernelGGL(fn, dim3((unsigned)((waves + per_wg - 1) / per_wg)), dim3(kStripThreads), 0, stream, a);

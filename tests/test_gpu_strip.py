@@ -33,13 +33,13 @@ def _compare(shape, dtype, corr, eq, chunks, seed, umax=0.1):
 D2_CASES = [  # (ny, nx), dtype, correction, equilibrium, step chunks
     ((2500, 512), "fp32_dev", False, "entropic", (4, 5, 6, 7, 100)),
     ((2500, 512), "fp64", True, "entropic", (6, 7, 8, 9, 10, 11, 100)),
-    # widths one off a multiple of the own columns (56 and 52), odd heights
-    ((3001, 337), "fp32_dev", True, "entropic", (4, 67)),
-    ((1801, 1093), "fp64", False, "entropic", (6, 71)),
-    ((1703, 1091), "fp64", True, "product", (12, 4)),
-    ((2011, 989), "fp64", False, "poly2", (13,)),
-    ((1201, 1009), "fp32_dev", False, "poly2", (9,)),
-    ((1999, 785), "fp32_dev", True, "product", (8,)),
+    # widths one off a multiple of the own columns (58 and 54), odd heights
+    ((3001, 349), "fp32_dev", True, "entropic", (4, 67)),
+    ((1801, 1081), "fp64", False, "entropic", (6, 71)),
+    ((1703, 1079), "fp64", True, "product", (12, 4)),
+    ((2011, 971), "fp64", False, "poly2", (13,)),
+    ((1201, 1045), "fp32_dev", False, "poly2", (9,)),
+    ((1999, 811), "fp32_dev", True, "product", (8,)),
     # the narrowest rows, and fewer rows than a sweep's halo (wrapped several times)
     ((30049, 64), "fp32_dev", False, "entropic", (12, 3)),
     ((30017, 65), "fp64", False, "entropic", (14,)),
