@@ -422,7 +422,9 @@ typedef struct lbm_pool_tuning {
                            advance two steps per launch, the intermediate state in LDS, in
                            runs where the class's slots that take at least two steps hold
                            >= 2^22 nodes (FP32) or 2^20 (FP64); a slot whose step count in
-                           the run is odd takes its last step in a one-step launch.  FP32:
+                           the run is odd takes its last step in a one-step launch.  With
+                           time_rows = 0 such a launch works in blocks of 62 x 14 nodes; with
+                           time_rows given, or persistent = 1, in sweeps.  Sweeps, FP32:
                            slots whose row, rounded up to 64, is at most 512 nodes (1024
                            with persistent = 1) run as whole-row tiles (no halo columns),
                            wider ones as column tiles of 512 (1024); FP64: column tiles of
@@ -436,8 +438,8 @@ typedef struct lbm_pool_tuning {
                            classes of such a pool run persistent as with time_block 0.
                            0 or 1: one step per launch */
     int32_t time_rows;  /* time_block = 2: rows swept by each whole-row sub-tile and each column
-                           tile (0 = default: 16; in the tile-ordered persistent form 16
-                           for FP32, 64 for FP64; at most 4096) */
+                           tile (0 = default: blocks; in the tile-ordered persistent form 16
+                           rows for FP32, 64 for FP64; at most 4096) */
     int32_t spin_log2;  /* persistent form: a workgroup waits at most 2^spin_log2 polls of the
                            grid barrier's counter, or of its tile's neighbours' counters,
                            before it reports a timeout (1..40; 0 = the

@@ -232,7 +232,7 @@ struct BlockArgs {
 __host__ __device__ constexpr int block_waves(int rpt) { return rpt == 1 ? 16 : 12; }
 
 template <int DT, bool CORR, int EQ, int RPT>
-__global__ __launch_bounds__(64 * block_waves(RPT)) void k_block2(BlockArgs a) {
+__device__ __forceinline__ void block2_tile(const BlockArgs &a, int tile) {
     using T = store_t<DT>;
     constexpr int NW = block_waves(RPT);
     __shared__ T edge[2][NW][6][64];
@@ -242,7 +242,6 @@ __global__ __launch_bounds__(64 * block_waves(RPT)) void k_block2(BlockArgs a) {
     const Gout dst = (Gout)a.dst;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = (int)blockDim.x >> 6;
     const int lane = (int)threadIdx.x & 63;
-    const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int nx = a.nx, ny = a.ny, h = a.K - 1;
     const int x0 = (tile % a.tiles_x) * a.own_x, y0 = (tile / a.tiles_x) * a.own_y;
     int x = (x0 - h + lane) % nx;
@@ -322,6 +321,11 @@ __global__ __launch_bounds__(64 * block_waves(RPT)) void k_block2(BlockArgs a) {
                 *(__attribute__((address_space(1))) T *)(row + i * psb + xb[1]) = f[j][i];
         }
     }
+}
+
+template <int DT, bool CORR, int EQ, int RPT>
+__global__ __launch_bounds__(64 * block_waves(RPT)) void k_block2(BlockArgs a) {
+    block2_tile<DT, CORR, EQ, RPT>(a, xcd_tile((int)blockIdx.x, (int)gridDim.x));
 }
 
 // One D1Q3 wavefront: K steps (1 .. h) of the strip's own columns.  h and tx are

@@ -137,7 +137,9 @@ static PoolStepFn pool_kernel(int dtype, bool corr, bool persistent) {
     }
 }
 
-// Two steps per launch in pools.  One launch has one workgroup shape.  FP32
+// Two steps per launch in pools: blocks (k_pool_block2), or, when the tuning
+// names the rows or the form is the tile-ordered persistent one, sweeps.  One
+// launch has one workgroup shape.  Sweeps, FP32
 // storage: 512 threads; a slot whose row, rounded up to 64, fits them runs as
 // whole-row tiles (two_step_rows_tile: floor(512 / w) sub-tiles of w lanes,
 // each sweeping its rows), wider slots as column tiles of 512.  Whole
@@ -191,6 +193,10 @@ static T2Geom t2_geom(int64_t nx, int64_t ny, int dtype, int R, bool persistent)
     }
     return g;
 }
+
+// Whether a class's launches of two steps take blocks (k_pool_block2) instead
+// of the sweeps above.
+static bool t2_blocks(const lbm_pool_tuning &t) { return !t.persistent && t.time_rows == 0; }
 
 // Slots that the tile-ordered persistent form may advance (D2Q9, FP64 or FP32
 // deviation storage, row-interleaved layout, persistent two-step tuning) carry
@@ -623,7 +629,16 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
         const bool pers = p->tun.persistent != 0;
         const int B = t2_block(cdtype, pers), TX = t2_cols(cdtype, pers);
         const int R = t2_rows(p->tun, cdtype);
-        auto geom = [&](int i) { return t2_geom(p->slots[i].d.cfg.nx, p->slots[i].d.cfg.ny, cdtype, R, pers); };
+        // launches of two steps take blocks, unless the tuning names the sweeps' rows
+        const bool blocks = two && t2_blocks(p->tun);
+        auto geom = [&](int i) {
+            const int64_t nx = p->slots[i].d.cfg.nx, ny = p->slots[i].d.cfg.ny;
+            if (!blocks)
+                return t2_geom(nx, ny, cdtype, R, pers);
+            T2Geom g;
+            g.tiles = ((nx + kPoolBlockCols - 1) / kPoolBlockCols) * ((ny + kPoolBlockRows - 1) / kPoolBlockRows);
+            return g;
+        };
         auto whole_w = [&](int i) { return geom(i).w; };  // whole-row sub-tile width, 0 for column tiles
         int nw = 0;  // slots in the whole-row part
         if (two) {
@@ -758,6 +773,11 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
                                       : (nt ? k_pool_step2<kF64, false, true> : k_pool_step2<kF64, false, false>))
                               : (corr ? (nt ? k_pool_step2<kDevF64, true, true> : k_pool_step2<kDevF64, true, false>)
                                       : (nt ? k_pool_step2<kDevF64, false, true> : k_pool_step2<kDevF64, false, false>));
+            if (blocks)
+                fn2 = dtype == kF64 ? (corr ? k_pool_block2<kF64, true> : k_pool_block2<kF64, false>)
+                                    : (corr ? k_pool_block2<kDevF64, true> : k_pool_block2<kDevF64, false>);
+            const dim3 block2((unsigned)(blocks ? 64 * kPoolBlockWaves : B));
+            const size_t lds2 = blocks ? 0 : lds;
             PoolStepFn fn1 = pool_kernel<2>(dtype, corr, false);
             // the larger LDS need of the two tile forms (whole-row: the most sub-tiles)
             PoolRunArgs a2 = a;
@@ -800,10 +820,10 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
                 // two-step tiles of the slots with s_j >= 2 L + 2: a prefix of each part
                 const int p1 = count_ge(0, nw, 2 * L + 2), p2 = count_ge(nw, n, 2 * L + 2);
                 if (p1 == nw) {
-                    launch(fn2, a2, 0, two_start[p2], dim3((unsigned)B), lds);
+                    launch(fn2, a2, 0, two_start[p2], block2, lds2);
                 } else {
-                    launch(fn2, a2, 0, two_start[p1], dim3((unsigned)B), lds);
-                    launch(fn2, a2, two_start[nw], two_start[p2], dim3((unsigned)B), lds);
+                    launch(fn2, a2, 0, two_start[p1], block2, lds2);
+                    launch(fn2, a2, two_start[nw], two_start[p2], block2, lds2);
                 }
                 // one-step tiles of the slots whose last step is 2 L + 1: a range of each part
                 const int q1 = count_ge(0, nw, 2 * L + 1), q2 = count_ge(nw, n, 2 * L + 1);

@@ -26,6 +26,7 @@
 #include <stdint.h>
 
 #include "kernels.hpp"
+#include "kernels_strip.hpp"
 #include "kernels_t2.hpp"
 #include "tile_deps.hpp"
 
@@ -165,6 +166,34 @@ __global__ __launch_bounds__(1024) void k_pool_step2(PoolRunArgs a) {
         two_step_rows_tile<DT, CORR, kEqEntropic, NT>(s, t - a.tile_start[lo], w, sub, a.t2_R);
     else
         two_step_tile<DT, CORR, kEqEntropic, NT>(s, t - a.tile_start[lo]);
+}
+
+// The same in blocks (block2_tile with two steps): tile_start counts
+// ceil(nx / 62) x ceil(ny / kPoolBlockRows) blocks a slot, eight wavefronts of two
+// rows each, two of them halo rows, like the outer two columns.  A block reads
+// its rows at once where the sweeps read them one after another between
+// barriers.  us per step, sweeps of 16 rows / blocks: 64 domains of 32..512 (4.9M
+// nodes) FP32 48.9 / 42.2, FP64 80.5 / 76.1; 512 such 326 / 314 and 570 / 569; 24 of
+// 500..1024 FP32 129 / 117.  Bound by HBM, at 4.2 TB/s of one read and one
+// write; eight wavefronts of two rows beat four to twelve of one, two or four
+// by 1-20 %.
+constexpr int kPoolBlockWaves = 8, kPoolBlockRows = 2 * kPoolBlockWaves - 2, kPoolBlockCols = 62;
+template <int DT, bool CORR>
+__global__ __launch_bounds__(64 * kPoolBlockWaves) void k_pool_block2(PoolRunArgs a) {
+    const int t = xcd_tile((int)blockIdx.x, (int)gridDim.x) + a.tile_base;
+    int lo = 0, hi = a.n - 1;  // last slot k with tile_start[k] <= t
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (a.tile_start[mid] <= t)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    const SlotDesc &dd = a.slots[lo];
+    const int nx = dd.nx, p = (dd.parity + a.step0) & 1;
+    const BlockArgs b{dd.buf[p], dd.buf[p ^ 1], nx, dd.ny, 2, kPoolBlockCols, kPoolBlockRows,
+                      (nx + kPoolBlockCols - 1) / kPoolBlockCols, dd.ps, dd.rs, dd.relax, dd.flag};
+    block2_tile<DT, CORR, kEqEntropic, 2>(b, t - a.tile_start[lo]);
 }
 
 // One step (a.step0) over the tiles [tile_base, tile_base + grid): the active
