@@ -170,4 +170,91 @@ __global__ __launch_bounds__(sweep3_columns(sizeof(store_t<DT>)))
     raise_flag(a.flag, bad && own);
 }
 
+// Two steps of a small block, for domains too small for sweeps.  A workgroup
+// takes a block of own_x x own_y x own_z nodes: its threads first collide step 1
+// at the block's nodes with one layer of halo around (populations pulled from
+// HBM) and put the values into LDS; behind the barrier the first own_x own_y
+// own_z threads take one own node each, pull from LDS, collide step 2 and store.
+//
+// Bound: latency (the gap between launches, the pulls, two collisions of up to
+// four wavefronts a SIMD); the halo makes two to three times the step-1
+// collisions.  us per step, one step per launch / blocks: 16^3 FP32 3.7 / 2.7, 32^3
+// FP64 5.0 / 3.8, 48^3 FP32 6.9 / 5.9, FP64 9.9 / 8.1; 64^3 FP32 10.2 / 11.2.
+struct Block3Args {
+    const void *src;
+    void *dst;
+    int nx, ny, nz;
+    int own_x, own_y, own_z;  // (own_x + 2) (own_y + 2) (own_z + 2) <= the workgroup's threads
+    int tiles_x, tiles_y;
+    int64_t ps, rs;
+    Relax relax;
+    int *flag;
+};
+
+// most threads of a workgroup: 27 values each in LDS
+__host__ __device__ constexpr int block3_threads(size_t elem) { return elem == 4 ? 1024 : 704; }
+__host__ __device__ constexpr size_t block3_lds_bytes(int threads, size_t elem) { return (size_t)27 * threads * elem; }
+
+template <int DT, bool CORR, int EQ>
+__global__ __launch_bounds__(block3_threads(sizeof(store_t<DT>))) void k_block3(Block3Args a) {
+    using T = store_t<DT>;
+    extern __shared__ __align__(16) unsigned char block3_lds[];
+    T *lds = reinterpret_cast<T *>(block3_lds);
+    const int N = (int)blockDim.x, t = (int)threadIdx.x;
+    const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int x0 = tile % a.tiles_x * a.own_x, y0 = tile / a.tiles_x % a.tiles_y * a.own_y,
+              z0 = tile / (a.tiles_x * a.tiles_y) * a.own_z;
+    const int W = a.own_x + 2, WH = W * (a.own_y + 2);
+    typedef const __attribute__((address_space(1))) char *Gin;
+    typedef __attribute__((address_space(1))) char *Gout;
+    const Gin src = (Gin)a.src;
+    const Gout dst = (Gout)a.dst;
+    const int64_t psb = a.ps * (int64_t)sizeof(T);
+    const uint32_t rsb = (uint32_t)(a.rs * (int64_t)sizeof(T));  // the whole buffer is below 4 GiB
+    bool bad = false;
+    if (t < WH * (a.own_z + 2)) {
+        const int lz = t / WH, r = t - lz * WH, ly = r / W, lx = r - ly * W;
+        auto wrap = [](int v, int n) {
+            v %= n;
+            return v < 0 ? v + n : v;
+        };
+        const int x = wrap(x0 + lx - 1, a.nx), y = wrap(y0 + ly - 1, a.ny), z = wrap(z0 + lz - 1, a.nz);
+        const uint32_t xo[3] = {(uint32_t)(x + 1 == a.nx ? 0 : x + 1) * (uint32_t)sizeof(T),
+                                (uint32_t)x * (uint32_t)sizeof(T),
+                                (uint32_t)(x == 0 ? a.nx - 1 : x - 1) * (uint32_t)sizeof(T)};  // x - c_x
+        const int ys[3] = {y + 1 == a.ny ? 0 : y + 1, y, y == 0 ? a.ny - 1 : y - 1};           // y - c_y
+        const int zs[3] = {z + 1 == a.nz ? 0 : z + 1, z, z == 0 ? a.nz - 1 : z - 1};           // z - c_z
+        T f[27];
+#pragma unroll
+        for (int i = 0; i < 27; ++i) {
+            const uint32_t o = (uint32_t)(zs[i / 9] * a.ny + ys[i / 3 % 3]) * rsb + xo[i % 3];
+            f[i] = *(const __attribute__((address_space(1))) T *)(src + i * psb + o);
+        }
+        // (flags: step 1's own nodes are this or a neighbouring block's, all real nodes)
+        bad = collide_dt<3, DT, CORR, EQ>(f, a.relax);
+#pragma unroll
+        for (int i = 0; i < 27; ++i)
+            lds[i * N + t] = f[i];
+    }
+    __syncthreads();
+    if (t < a.own_x * a.own_y * a.own_z) {
+        const int oxy = a.own_x * a.own_y;
+        const int lz = t / oxy, r = t - lz * oxy, ly = r / a.own_x, lx = r - ly * a.own_x;
+        const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+        if (x < a.nx && y < a.ny && z < a.nz) {
+            const T *at = lds + (lz + 1) * WH + (ly + 1) * W + lx + 1;
+            T g[27];
+#pragma unroll
+            for (int i = 0; i < 27; ++i)
+                g[i] = at[i * N - (i / 9 - 1) * WH - (i / 3 % 3 - 1) * W - (i % 3 - 1)];
+            bad |= collide_dt<3, DT, CORR, EQ>(g, a.relax);
+            const uint32_t o = (uint32_t)(z * a.ny + y) * rsb + (uint32_t)x * (uint32_t)sizeof(T);
+#pragma unroll
+            for (int i = 0; i < 27; ++i)
+                *(__attribute__((address_space(1))) T *)(dst + i * psb + o) = g[i];
+        }
+    }
+    raise_flag(a.flag, bad);
+}
+
 }  // namespace lbm

@@ -342,10 +342,8 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
         L.deep = strip1_steps(cfg->nx);
     else if (automatic && L.dim == 2)
         plan2(cfg, L);
-    else if (automatic && sweep3_takes(cfg, L))
-        L.deep = 2;
-    if (L.deep && L.dim == 3)
-        L.sweep3 = sweep3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem);
+    else if (automatic)
+        plan3(cfg, L);
     L.red_blocks = (int)std::min<int64_t>(1024, (L.n + kReduceThreads - 1) / kReduceThreads);
     // workspace: buffer A | buffer B | flag block (256 B) | diag out (256 B) | partials
     L.off_buf[0] = 0;
@@ -827,6 +825,7 @@ static int enqueue_deep(lbm_handle *h, int cur, int K, hipStream_t s) {
     return d.L.dim == 1   ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
            : d.L.block2.rpt ? launch_block2(d.L, a, d.cfg.dtype, corr, K, s)
            : d.L.dim == 2 ? launch_strip2(d.L, a, d.cfg.dtype, corr, K, s)
+           : d.L.block3.own_x ? launch_block3(d.L, a, d.cfg.dtype, corr, s)
                           : launch_sweep3(d.L, a, d.cfg.dtype, corr, s);
 }
 

@@ -17,6 +17,12 @@ struct Sweep3Geom {
     int w, rows, planes;
 };
 
+// Block of a small D3Q27 domain (sweep3.hip): own nodes per axis (0: the domain
+// takes no blocks) and threads of a workgroup.
+struct Block3Geom {
+    int own_x, own_y, own_z, threads;
+};
+
 // Tiling of a small D2Q9 domain's blocks (strip.hip): rows per wavefront (0: the
 // domain takes no blocks), wavefronts, own columns and rows per workgroup.
 struct Block2Geom {
@@ -41,6 +47,7 @@ struct Layout {
     int strip_rows[2]; // D2Q9 strips: own rows per wavefront with 4 and with 6 steps
     Block2Geom block2; // D2Q9 blocks
     Sweep3Geom sweep3; // D3Q27 sweeps
+    Block3Geom block3; // D3Q27 blocks
     bool zhalo;        // z-slab: each buffer holds halo planes -1 and nz around the nz planes
     int64_t plane;     // elements of one plane (rows layout: ny * rs)
     int red_blocks;    // workgroups of the moments reduction
@@ -80,11 +87,12 @@ int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, i
 
 int launch_block2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
 
-// Two-step D3Q27 sweeps (sweep3.hip).
-constexpr size_t kSweep3Bytes = (size_t)96 << 20;  // both population buffers from here on
-bool sweep3_takes(const lbm_config *cfg, const Layout &L);
-Sweep3Geom sweep3_geom(int64_t nx, int64_t ny, int64_t nz, size_t elem);
+// Two-step D3Q27 sweeps and blocks (sweep3.hip).
+constexpr size_t kSweep3Bytes = (size_t)96 << 20;  // sweeps: both population buffers from here on
+constexpr int64_t kBlock3Nodes = 200000;           // blocks: domains up to here
+void plan3(const lbm_config *cfg, Layout &L);
 int launch_sweep3(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
+int launch_block3(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
 
 // Bind a domain to its workspace and enqueue f = f^eq(rho, u) plus the flag
 // clear; the caller synchronises and reads the flag (domain_read_flag).

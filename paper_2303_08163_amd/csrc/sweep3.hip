@@ -1,8 +1,9 @@
-// sweep3.hip -- host side of the two-step D3Q27 sweep (kernels_sweep3.hpp): which
-// domains take it, its geometry and launches.
+// sweep3.hip -- host side of the two-step D3Q27 sweeps and blocks
+// (kernels_sweep3.hpp): which domains take them, their geometry and launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "kernels_sweep3.hpp"
 #include "lbm_internal.hpp"
@@ -56,17 +57,63 @@ Sweep3Geom sweep3_geom(int64_t nx, int64_t ny, int64_t nz, size_t elem) {
     return best;
 }
 
-// Whether runs of a domain take two steps per launch (us per step, one step per
-// launch against two: FP32 64^3 10.2 / 12.0, 80^3 19.2 / 18.0, 128^3 86 / 60, 256^3
-// 630 / 435; FP64 64^3 17.6 / 15.9, 128^3 164 / 98, 256^3 1267 / 736).
-bool sweep3_takes(const lbm_config *cfg, const Layout &L) {
+// Block of k_block3 with the least estimated time, and that time in us per
+// launch: a fixed part, a part for each round of workgroups that share the
+// compute units, and for each workgroup of a compute unit its wavefronts in
+// step 1 and step 2 and the 128-byte lines of its row runs.  (Fitted to 20^3 ..
+// 56^3; the block it picks is within 7 % of the best one measured there: 32^3
+// FP32 16 x 2 x 4 own 6.8, 48^3 FP32 12 x 6 x 6 11.8, 48^3 FP64 16 x 4 x 4 16.2.)
+static Block3Geom block3_geom(int64_t nx, int64_t ny, int64_t nz, size_t elem, double *us) {
+    const bool f32 = elem == 4;
+    const double fixed = f32 ? 3.2 : 2.4, per_round = f32 ? 1.3 : 1.95, wave1 = 0.145, wave2 = f32 ? 0.40 : 0.575,
+                 line = 0.0205;
+    Block3Geom best{};
+    *us = -1.0;
+    for (int ox : {8, 12, 16, 20, 24, 32, 48})
+        for (int oy = 1; oy <= 12; ++oy)
+            for (int oz = 1; oz <= 12; ++oz) {
+                const int threads = ((ox + 2) * (oy + 2) * (oz + 2) + 63) / 64 * 64;
+                if (threads > block3_threads(elem) || oy > ny || oz > nz)
+                    continue;
+                const int64_t wgs = ((nx + ox - 1) / ox) * ((ny + oy - 1) / oy) * ((nz + oz - 1) / oz);
+                const double rounds = (double)((wgs + 255) / 256);
+                const int share = std::max(1, std::min((int)(163840 / block3_lds_bytes(threads, elem)),
+                                                       (f32 ? 2048 : 1280) / threads));
+                const double lines = (double)((oy + 2) * (oz + 2) * ((ox + 10 + 31) / 32));
+                const double t = fixed + per_round * std::ceil(rounds / share) +
+                                 rounds * (wave1 * (threads / 64) + wave2 * ((ox * oy * oz + 63) / 64) + line * lines);
+                if (*us < 0.0 || t < *us) {
+                    *us = t;
+                    best = Block3Geom{ox, oy, oz, threads};
+                }
+            }
+    return best;
+}
+
+// Which form the runs of a D3Q27 domain take: sweeps, blocks (small domains), or
+// one step per launch.  us per step, one step per launch against sweeps: FP32 64^3
+// 10.2 / 12.0, 80^3 19.2 / 18.0, 128^3 86 / 60, 256^3 630 / 435; FP64 64^3 17.6 /
+// 15.9, 128^3 164 / 98, 256^3 1267 / 736.
+void plan3(const lbm_config *cfg, Layout &L) {
     if (L.dim != 3 || L.zhalo || L.layout != LBM_LAYOUT_ROWS ||
         (cfg->dtype != LBM_FP64 && cfg->dtype != LBM_FP32_DEV))
-        return false;
-    // byte offsets inside a plane are 32-bit
-    if (L.plane * (int64_t)L.elem >= ((int64_t)1 << 31))
-        return false;
-    return cfg->nx >= 16 && cfg->ny >= 4 && 2 * L.buf_bytes > kSweep3Bytes;
+        return;
+    // byte offsets inside a plane (a block: inside the buffer) are 32-bit
+    if (2 * L.buf_bytes > kSweep3Bytes && cfg->nx >= 16 && cfg->ny >= 4 &&
+        L.plane * (int64_t)L.elem < ((int64_t)1 << 31)) {
+        L.sweep3 = sweep3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem);
+        L.deep = 2;
+    } else if (L.n <= kBlock3Nodes) {
+        // one step per launch took about (us) 3.2 + 0.034 n / 1000 with FP32 storage,
+        // 4.0 + 0.056 n / 1000 with FP64 (16^3 3.7 / 4.2, 40^3 5.5 / 7.5, 56^3 9.2 / 14.5)
+        const double one = L.elem == 4 ? 3.2 + 0.034e-3 * (double)L.n : 4.0 + 0.056e-3 * (double)L.n;
+        double us;
+        const Block3Geom g = block3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem, &us);
+        if (us > 0.0 && us / 2 < 0.86 * one) {  // (the estimate runs up to 15 % low)
+            L.block3 = g;
+            L.deep = 2;
+        }
+    }
 }
 
 template <int DT, int EQ, bool CORR>
@@ -108,6 +155,32 @@ int launch_sweep3(const Layout &L, const StepArgs &s, int dtype, bool corr, hipS
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return hip_fail(e, "sweep launch");
+    return LBM_OK;
+}
+
+template <int DT>
+static void (*block3_kernel(int eq, bool corr))(Block3Args) {
+    switch (eq) {
+    case LBM_EQ_POLY2:
+        return corr ? k_block3<DT, true, kEqPoly2> : k_block3<DT, false, kEqPoly2>;
+    case LBM_EQ_PRODUCT:
+        return corr ? k_block3<DT, true, kEqProduct> : k_block3<DT, false, kEqProduct>;
+    default:
+        return corr ? k_block3<DT, true, kEqEntropic> : k_block3<DT, false, kEqEntropic>;
+    }
+}
+
+int launch_block3(const Layout &L, const StepArgs &s, int dtype, bool corr, hipStream_t stream) {
+    const Block3Geom &g = L.block3;
+    const int tx = (s.nx + g.own_x - 1) / g.own_x, ty = (s.ny + g.own_y - 1) / g.own_y,
+              tz = (s.nz + g.own_z - 1) / g.own_z;
+    const Block3Args a{s.src, s.dst, s.nx, s.ny, s.nz, g.own_x, g.own_y, g.own_z, tx, ty, L.ps, L.rs, s.relax, s.flag};
+    void (*fn)(Block3Args) = dtype == kF64 ? block3_kernel<kF64>(L.eq, corr) : block3_kernel<kDevF64>(L.eq, corr);
+    hipLaunchKernelGGL(fn, dim3((unsigned)(tx * ty * tz)), dim3((unsigned)g.threads),
+                       (unsigned)block3_lds_bytes(g.threads, L.elem), stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return hip_fail(e, "block launch");
     return LBM_OK;
 }
 

@@ -1,4 +1,5 @@
-"""Two-step D3Q27 sweeps (the default of large periodic domains): bitwise the
+"""Two-step D3Q27 launches, sweeps (large domains) and blocks (small ones), the
+default of periodic domains: bitwise the
 one-step-per-launch run (time_block = 1), on ragged extents, both storage
 types, every equilibrium, odd step counts and graph replays."""
 import numpy as np
@@ -64,10 +65,41 @@ def test_sweep_equals_one_step_bitwise(case):
         assert da == db
 
 
+BLOCK_CASES = [  # (nz, ny, nx), dtype, correction, equilibrium, step chunks
+    ((16, 16, 16), "fp32_dev", False, "entropic", (1, 2, 3, 66)),
+    ((48, 48, 48), "fp32_dev", True, "entropic", (2, 5, 64)),
+    ((48, 48, 48), "fp64", False, "entropic", (2, 3)),
+    ((17, 23, 31), "fp64", True, "product", (4, 1)),
+    ((33, 12, 25), "fp32_dev", False, "poly2", (7,)),
+    # fewer nodes than a block and its halo along an axis
+    ((1, 1, 1), "fp64", False, "entropic", (4,)),
+    ((3, 4, 5), "fp32_dev", True, "entropic", (6, 65)),
+    ((1, 40, 9), "fp64", False, "poly2", (2,)),
+    ((50, 2, 3), "fp32_dev", True, "product", (4,)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(BLOCK_CASES)))
+def test_block_equals_one_step_bitwise(case):
+    import torch
+    lbm = _lbm()
+    shape, dtype, corr, eq, chunks = BLOCK_CASES[case]
+    rho0, u0 = _fields(shape, 700 + case)
+    kw = dict(dtype=dtype, bulk_correction=corr, equilibrium=eq)
+    with lbm.Domain(rho0, u0, 0.55, **kw) as a, \
+            lbm.Domain(rho0, u0, 0.55, tuning=lbm.make_tuning(time_block=1), **kw) as b:
+        for n in chunks:
+            a.step(n)
+            b.step(n)
+            assert torch.equal(_state(a), _state(b)), (shape, n)
+
+
 def test_sweep_raises_the_domain_flag_as_one_step():
     lbm = _lbm()
-    for umax, lo, hi in ((0.99, 0.3, 2.0), (0.97, 0.5, 1.5), (0.2, 0.9, 1.1)):
-        rho0, u0 = _fields((130, 128, 128), 9, umax, lo, hi)
+    for shape, umax, lo, hi in (((130, 128, 128), 0.99, 0.3, 2.0), ((130, 128, 128), 0.2, 0.9, 1.1),
+                                ((20, 24, 28), 0.99, 0.3, 2.0), ((20, 24, 28), 0.97, 0.5, 1.5),
+                                ((20, 24, 28), 0.2, 0.9, 1.1)):
+        rho0, u0 = _fields(shape, 9, umax, lo, hi)
         with lbm.Domain(rho0, u0, 0.5001, dtype="fp32_dev") as a, \
                 lbm.Domain(rho0, u0, 0.5001, dtype="fp32_dev", tuning=lbm.make_tuning(time_block=1)) as b:
             for n in (2, 4):
