@@ -345,8 +345,8 @@ int lbm_energy(lbm_handle *h, const double *U, double rho_ref, double *out);
  *   U, rho_ref  as for lbm_energy.
  *   out    device pointer to steps / every + 1 doubles: out[k] is the energy
  *          after k * every steps, written when the stream reaches it.
- * The same kernels run in the same order as the calls made one by one, so the
- * values and the final state are bitwise theirs.  Returns without
+ * The values and the final state are bitwise those of the calls made one by
+ * one; short D1Q3 rows take the whole history in one launch.  Returns without
  * synchronising.  Errors: LBM_EINVAL (those of lbm_energy; every < 1, steps
  * < 0 or not a multiple of every; a z-slab domain), checked before anything is
  * enqueued; LBM_EDEVICE (the work enqueued before the failing launch stays

@@ -697,6 +697,23 @@ __device__ __forceinline__ double block_sum(double v) {
     return r;
 }
 
+// One node's term; half_cs2_over_rho = c_s^2 / (2 rho_ref).
+template <int DIM>
+__device__ __forceinline__ double node_energy(const double (&f)[Lattice<DIM>::Q], double rho0, double rho_ref,
+                                              double half_cs2_over_rho, const double (&U)[3]) {
+    double rho, j[3];
+    node_moments<DIM>(f, rho0, rho, j);
+    const double inv = 1.0 / rho;
+    double du2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        const double du = j[d] * inv - U[d];
+        du2 = fma(du, du, du2);
+    }
+    const double dr = rho - rho_ref;
+    return fma(0.5 * rho_ref, du2, (dr * dr) * half_cs2_over_rho);
+}
+
 template <int DIM, bool DEV>
 __global__ __launch_bounds__(kReduceThreads) void k_energy(EnergyArgs a) {
     using T = store_t<DEV>;
@@ -711,17 +728,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_energy(EnergyArgs a) {
 #pragma unroll
         for (int i = 0; i < Q; ++i)
             f[i] = (double)p[i * a.ps];
-        double rho, j[3];
-        node_moments<DIM>(f, DEV ? a.rho0 : 0.0, rho, j);
-        const double inv = 1.0 / rho;
-        double du2 = 0.0;
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-            const double du = j[d] * inv - a.U[d];
-            du2 = fma(du, du, du2);
-        }
-        const double dr = rho - a.rho_ref;
-        acc += fma(0.5 * a.rho_ref, du2, (dr * dr) * half_cs2_over_rho);
+        acc += node_energy<DIM>(f, DEV ? a.rho0 : 0.0, a.rho_ref, half_cs2_over_rho, a.U);
     }
     double r = block_sum(acc);
     if (!last_workgroup(a.arrived, [&] { put_partial(a.partials + blockIdx.x, r); }))

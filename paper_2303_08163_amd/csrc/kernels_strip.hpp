@@ -36,6 +36,18 @@ __device__ __forceinline__ T lane_move(T v) {
         return __builtin_bit_cast(T, r);
     }
 }
+// Value of one lane (uniform index).
+template <typename T>
+__device__ __forceinline__ T lane_read(T v, int lane) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+    } else {
+        int2 b = __builtin_bit_cast(int2, v);
+        b.x = __builtin_amdgcn_readlane(b.x, lane);
+        b.y = __builtin_amdgcn_readlane(b.y, lane);
+        return __builtin_bit_cast(T, b);
+    }
+}
 // g[k] <- the value that the population with c_x = cx - 1 pulls into column k.
 template <typename T, int NC>
 __device__ __forceinline__ void pull_columns(const T (&f)[NC], int cx, T (&g)[NC]) {
@@ -410,6 +422,123 @@ __global__ __launch_bounds__(kStripThreads) void k_strip1(StripArgs a) {
                 for (int i = 0; i < 3; ++i)
                     dst[i * a.ps + x0 + own + k] = f[i][k];
     }
+}
+
+// A whole short D1Q3 row in one workgroup, one node per thread: any number of
+// steps in one launch, with the populations in registers, and the acoustic
+// energies of a history on the way.
+//
+// Bound: the dependence chain of one collision (one wavefront per SIMD up to
+// 256 nodes), 0.19 us per step within one wavefront, 0.25 with the exchange
+// through LDS; a launch of at most 16 steps costs the strips 0.55 us per step
+// on such rows.
+constexpr int kRowMax = 1024;  // nodes, one workgroup's threads
+
+struct RowArgs {
+    const void *src;
+    void *dst;
+    int nx;
+    int steps;  // steps of this launch
+    int every;  // steps between readings (energies only)
+    bool first; // a reading before the first step
+    int64_t ps;
+    Relax relax;
+    int *flag;
+    double *out;  // energies (NULL: none), one per reading
+    double rho_ref;
+    double U[3];
+};
+
+// The neighbours' values come by a lane move (ONE: the row fits one wavefront,
+// whose ends are read as scalars) or through LDS with one barrier per step.
+// A reading's wavefront sums are folded after the next barrier; the order of
+// the sum is k_energy's, so the energies are bitwise its.
+template <int DT, bool CORR, int EQ, bool ONE, bool ENERGY>
+__global__ __launch_bounds__(ONE ? 64 : kRowMax) void k_row1(RowArgs a) {
+    using T = store_t<DT>;
+    constexpr int N = ONE ? 1 : kRowMax;
+    __shared__ T edge[2][2][N];
+    __shared__ double sums[2][kRowMax / 64];
+    const int x = (int)threadIdx.x, nx = a.nx;
+    const bool in = x < nx;
+    const int waves = (nx + 63) / 64;
+    const int left = x == 0 ? nx - 1 : x - 1, right = x + 1 >= nx ? 0 : x + 1;
+    T f[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        f[i] = static_cast<const T *>(a.src)[i * a.ps + (in ? x : nx - 1)];
+    const double half_cs2_over_rho = (1.0 / 6.0) / a.rho_ref;
+    double *out = a.out;
+    int slot = 0;
+    // this wavefront's part of a reading / the whole of it, by thread 0
+    auto put_energy = [&]() {
+        const double v[3] = {(double)f[0], (double)f[1], (double)f[2]};
+        const double e = node_energy<1>(v, DT == kF64 ? 0.0 : a.relax.rho0, a.rho_ref, half_cs2_over_rho, a.U);
+        const double r = wave_sum(in ? e : 0.0);
+        slot ^= 1;
+        if ((x & 63) == 0)
+            sums[slot][x >> 6] = r;
+    };
+    auto store_energy = [&]() {
+        if (x == 0) {
+            double part[4];  // sums of 256 nodes, as the workgroups of k_energy leave them
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                part[b] = 4 * b < waves ? sums[slot][4 * b] : 0.0;
+#pragma unroll
+                for (int w = 1; w < 4; ++w)
+                    part[b] += 4 * b + w < waves ? sums[slot][4 * b + w] : 0.0;
+            }
+            *out = (part[0] + part[2]) + (part[1] + part[3]);
+        }
+        ++out;
+    };
+    bool pending = false;  // a reading waits for the next barrier
+    if (ENERGY && a.first) {
+        put_energy();
+        pending = true;
+    }
+    int to_reading = a.every;
+    bool bad = false;
+    for (int s = 0; s < a.steps; ++s) {
+        T v[3] = {f[0], f[1], f[2]};
+        if constexpr (ONE) {
+            const T up = lane_move<true>(f[0]), down = lane_move<false>(f[2]);
+            const T head = lane_read(f[0], 0), tail = lane_read(f[2], nx - 1);
+            v[0] = right == 0 ? head : up;
+            v[2] = x == 0 ? tail : down;
+        } else {
+            edge[s & 1][0][x] = f[0];
+            edge[s & 1][1][x] = f[2];
+            __syncthreads();
+            v[0] = edge[s & 1][0][right];
+            v[2] = edge[s & 1][1][left];
+        }
+        if (ENERGY && pending) {
+            if (ONE)
+                __syncthreads();
+            store_energy();
+            pending = false;
+        }
+        bad |= collide_dt<1, DT, CORR, EQ>(v, a.relax);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            f[i] = v[i];
+        if (ENERGY && --to_reading == 0) {
+            to_reading = a.every;
+            put_energy();
+            pending = true;
+        }
+    }
+    if (ENERGY && pending) {
+        __syncthreads();
+        store_energy();
+    }
+    raise_flag(a.flag, bad && in);
+    if (in)
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            static_cast<T *>(a.dst)[i * a.ps + x] = f[i];
 }
 
 }  // namespace lbm

@@ -337,10 +337,15 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
     }
     L.buf_bytes = (size_t)elems * L.elem;
     // runs left to the library take more steps per launch than time_block where they pay
-    L.deep = 0;
-    if (automatic && L.dim == 1 && L.tblock > 1)
-        L.deep = strip1_steps(cfg->nx);
-    else if (automatic && L.dim == 2)
+    L.deep = L.row = 0;
+    if (automatic && L.dim == 1) {
+        if (cfg->dtype == LBM_FP64 || cfg->dtype == LBM_FP32_DEV)
+            L.row = row1_plan(cfg->nx);
+        if (L.row == 1)
+            L.deep = kRowSteps;
+        else if (L.tblock > 1)
+            L.deep = strip1_steps(cfg->nx);
+    } else if (automatic && L.dim == 2)
         plan2(cfg, L);
     else if (automatic)
         plan3(cfg, L);
@@ -822,7 +827,8 @@ static int enqueue_deep(lbm_handle *h, int cur, int K, hipStream_t s) {
     StepArgs a{d.buf[cur], d.buf[cur ^ 1], (int)d.cfg.nx, (int)d.cfg.ny, (int)d.cfg.nz, 0, 0,
                d.L.ps, d.L.rs, d.relax, d.flag, 0};
     const bool corr = d.cfg.bulk_correction != 0;
-    return d.L.dim == 1   ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
+    return d.L.row == 1   ? launch_row1(d.L, a, d.cfg.dtype, corr, K, nullptr, s)
+           : d.L.dim == 1 ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
            : d.L.block2.rpt ? launch_block2(d.L, a, d.cfg.dtype, corr, K, s)
            : d.L.dim == 2 ? launch_strip2(d.L, a, d.cfg.dtype, corr, K, s)
            : d.L.block3.own_x ? launch_block3(d.L, a, d.cfg.dtype, corr, s)
@@ -847,7 +853,7 @@ static int next_steps(const Layout &L, int64_t n) {
 static int enqueue_steps(lbm_handle *h, int cur, int K, hipStream_t s) {
     if (K == 1)
         return enqueue_step(h, cur, s);
-    if (K == h->d.L.tblock)
+    if (K == h->d.L.tblock && !h->d.L.row)
         return enqueue_pair(h, cur, s);
     return enqueue_deep(h, cur, K, s);
 }
@@ -1039,11 +1045,7 @@ int lbm_moments(lbm_handle *h, double *rho, double *u, lbm_diag *diag) {
     return domain_moments(h->d, h->stream, rho, u, diag, h->host);
 }
 
-int lbm_energy(lbm_handle *h, const double *U, double rho_ref, double *out) {
-    if (!h || !out) {
-        set_error("NULL handle or output");
-        return LBM_EINVAL;
-    }
+static int check_reference(const lbm_handle *h, const double *U, double rho_ref) {
     if (!(rho_ref > 0.0) || !std::isfinite(rho_ref)) {
         set_error("rho_ref must be finite and > 0");
         return LBM_EINVAL;
@@ -1054,7 +1056,38 @@ int lbm_energy(lbm_handle *h, const double *U, double rho_ref, double *out) {
                 set_error("U must be finite");
                 return LBM_EINVAL;
             }
+    return LBM_OK;
+}
+
+int lbm_energy(lbm_handle *h, const double *U, double rho_ref, double *out) {
+    if (!h || !out) {
+        set_error("NULL handle or output");
+        return LBM_EINVAL;
+    }
+    const int rc = check_reference(h, U, rho_ref);
+    if (rc != LBM_OK)
+        return rc;
     return domain_energy(h->d, h->stream, U, rho_ref, out);
+}
+
+// A short row's history: steps and readings in one launch, or in as many as
+// kRowSteps steps each make.
+static int row_history(lbm_handle *h, int64_t steps, int64_t every, const double *U, double rho_ref, double *out) {
+    int rc = check_reference(h, U, rho_ref);
+    DomainState &d = h->d;
+    const int most = (int)(kRowSteps / every * every);
+    for (int64_t s = 0; rc == LBM_OK && s < steps;) {
+        const int K = (int)std::min<int64_t>(most, steps - s);
+        const RowEnergy e{s ? out + s / every + 1 : out, (int)every, s == 0, rho_ref, U ? U[0] : 0.0};
+        StepArgs a{d.buf[d.cur], d.buf[d.cur ^ 1], (int)d.cfg.nx, 1, 1, 0, 0, d.L.ps, d.L.rs, d.relax, d.flag, 0};
+        rc = launch_row1(d.L, a, d.cfg.dtype, d.cfg.bulk_correction != 0, K, &e, h->stream);
+        if (rc == LBM_OK) {
+            d.cur ^= 1;
+            d.steps += K;
+            s += K;
+        }
+    }
+    return rc;
 }
 
 int lbm_energy_history(lbm_handle *h, int64_t steps, int64_t every, const double *U, double rho_ref, double *out) {
@@ -1066,6 +1099,8 @@ int lbm_energy_history(lbm_handle *h, int64_t steps, int64_t every, const double
         set_error("a z-slab's steps need halo exchanges between them");
         return LBM_EINVAL;
     }
+    if (h->d.L.row && steps > 0 && every <= kRowSteps)
+        return row_history(h, steps, every, U, rho_ref, out);
     int rc = lbm_energy(h, U, rho_ref, out);  // also checks U and rho_ref
     for (int64_t k = 1; rc == LBM_OK && k <= steps / every; ++k) {
         rc = lbm_step(h, every);

@@ -44,6 +44,7 @@ struct Layout {
     int tblock;        // LBGK steps per launch (1; 2 on D2Q9; 2, 4 or 8 on D1Q3)
     int t2_tx, t2_rows;  // multi-step kernels: owned columns (nodes) and rows per workgroup
     int deep;          // steps of the longest launch of a run (strips, sweeps; 0: tblock)
+    int row;           // 1: D1Q3 runs, 2: histories only, in one workgroup (k_row1)
     int strip_rows[2]; // D2Q9 strips: own rows per wavefront with 4 and with 6 steps
     Block2Geom block2; // D2Q9 blocks
     Sweep3Geom sweep3; // D3Q27 sweeps
@@ -83,6 +84,17 @@ void plan2(const lbm_config *cfg, Layout &L);
 int strip1_steps(int64_t nx);
 int strip1_cols(int64_t nx, int dtype, int K);
 int launch_strip1(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
+// Short D1Q3 rows in one workgroup, with the readings of an energy history (NULL: none).
+constexpr int kRowSteps = 16384;  // most steps per launch
+struct RowEnergy {
+    double *out;
+    int every;
+    bool first;  // a reading before the first step
+    double rho_ref, U;
+};
+int row1_plan(int64_t nx);
+int launch_row1(const Layout &L, const StepArgs &args, int dtype, bool corr, int steps, const RowEnergy *e,
+                hipStream_t s);
 int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
 
 int launch_block2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);

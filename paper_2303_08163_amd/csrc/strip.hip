@@ -226,4 +226,56 @@ int launch_strip1(const Layout &L, const StepArgs &s, int dtype, bool corr, int 
     return LBM_OK;
 }
 
+// D1Q3 rows in one workgroup.
+template <int DT, bool CORR, int EQ>
+static void (*row1_kernel(bool one, bool energy))(RowArgs) {
+    return one ? (energy ? k_row1<DT, CORR, EQ, true, true> : k_row1<DT, CORR, EQ, true, false>)
+               : (energy ? k_row1<DT, CORR, EQ, false, true> : k_row1<DT, CORR, EQ, false, false>);
+}
+template <int DT, bool CORR>
+static void (*row1_eq(int eq, bool one, bool energy))(RowArgs) {
+    return eq == LBM_EQ_POLY2     ? row1_kernel<DT, CORR, kEqPoly2>(one, energy)
+           : eq == LBM_EQ_PRODUCT ? row1_kernel<DT, CORR, kEqProduct>(one, energy)
+                                  : row1_kernel<DT, CORR, kEqEntropic>(one, energy);
+}
+
+// One compute unit against the strips' whole chip: a row up to one wavefront per
+// SIMD is bound by the latency of a step either way and spares the launches,
+// beyond two the unit's arithmetic is slower.  us per step of a long run with
+// the correction, strips and row: FP64 64 nodes 0.56 and 0.19, 256 0.53 and 0.25, 512
+// 0.55 and 0.37, 768 0.55 and 0.48, 1024 0.55 and 0.60; ten steps at 768 nodes
+// take 5.3 and 6.9 us.  A history also spares the energy's launch: 10 steps and
+// a reading at 64 nodes 8.0 and 2.6 us, at 1024 8.4 and 6.7 (FP32 8.6 and 7.2).
+int row1_plan(int64_t nx) { return nx <= 512 ? 1 : nx <= kRowMax ? 2 : 0; }
+
+int launch_row1(const Layout &L, const StepArgs &s, int dtype, bool corr, int steps, const RowEnergy *e,
+                hipStream_t stream) {
+    RowArgs a{};
+    a.src = s.src;
+    a.dst = s.dst;
+    a.nx = s.nx;
+    a.steps = steps;
+    a.ps = L.ps;
+    a.relax = s.relax;
+    a.flag = s.flag;
+    a.rho_ref = 1.0;
+    if (e) {
+        a.every = e->every;
+        a.first = e->first;
+        a.out = e->out;
+        a.rho_ref = e->rho_ref;
+        a.U[0] = e->U;
+    }
+    const int waves = (s.nx + 63) / 64;
+    const bool one = waves == 1;
+    void (*fn)(RowArgs) = dtype == kF64 ? (corr ? row1_eq<kF64, true>(L.eq, one, e) : row1_eq<kF64, false>(L.eq, one, e))
+                                        : (corr ? row1_eq<kDevF64, true>(L.eq, one, e)
+                                                : row1_eq<kDevF64, false>(L.eq, one, e));
+    hipLaunchKernelGGL(fn, dim3(1), dim3(64u * (unsigned)waves), 0, stream, a);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess)
+        return hip_fail(err, "row launch");
+    return LBM_OK;
+}
+
 }  // namespace lbm
