@@ -421,10 +421,11 @@ typedef struct lbm_pool_tuning {
     int32_t time_block; /* 2: D2Q9 classes (LBM_FP64 or LBM_FP32_DEV, row-interleaved slots)
                            advance two steps per launch, the intermediate state in LDS, in
                            runs where the class's slots that take at least two steps hold
-                           >= 2^22 nodes (FP32) or 2^20 (FP64); a slot whose step count in
+                           >= 4096 nodes; a slot whose step count in
                            the run is odd takes its last step in a one-step launch.  With
                            time_rows = 0 such a launch works in blocks of 62 x 14 nodes; with
-                           time_rows given, or persistent = 1, in sweeps.  Sweeps, FP32:
+                           time_rows given, or persistent = 1, in sweeps, and from 2^22
+                           (FP32) or 2^20 (FP64) nodes.  Sweeps, FP32:
                            slots whose row, rounded up to 64, is at most 512 nodes (1024
                            with persistent = 1) run as whole-row tiles (no halo columns),
                            wider ones as column tiles of 512 (1024); FP64: column tiles of

@@ -70,6 +70,14 @@ __device__ __forceinline__ int xcd_tile(int w, int count) {
     return xcd * per + (xcd < rem ? xcd : rem) + k;
 }
 
+// The same with each XCD's range walked backwards.
+__device__ __forceinline__ int xcd_tile(int w, int count, bool back) {
+    const int per = count / kXcds, rem = count % kXcds;
+    const int xcd = w % kXcds, k = w / kXcds;
+    const int own = per + (xcd < rem ? 1 : 0);
+    return xcd * per + (xcd < rem ? xcd : rem) + (back ? own - 1 - k : k);
+}
+
 // Record that some node of the calling wavefront left the equilibrium's
 // domain: one store per wavefront (by its first active lane), not one atomic
 // per node, so a domain that has blown up costs no more per step than a

@@ -243,11 +243,11 @@ struct BlockArgs {
 // most wavefronts of a workgroup: 128 registers a lane with one row, 168 with two
 __host__ __device__ constexpr int block_waves(int rpt) { return rpt == 1 ? 16 : 12; }
 
-template <int DT, bool CORR, int EQ, int RPT>
+// NW: most wavefronts; NB: exchange buffers (1 for a single exchange, K = 2).
+template <int DT, bool CORR, int EQ, int RPT, int NW = block_waves(RPT), int NB = 2>
 __device__ __forceinline__ void block2_tile(const BlockArgs &a, int tile) {
     using T = store_t<DT>;
-    constexpr int NW = block_waves(RPT);
-    __shared__ T edge[2][NW][6][64];
+    __shared__ T edge[NB][NW][6][64];
     typedef const __attribute__((address_space(1))) char *Gin;
     typedef __attribute__((address_space(1))) char *Gout;
     const Gin src = (Gin)a.src;
@@ -289,7 +289,7 @@ __device__ __forceinline__ void block2_tile(const BlockArgs &a, int tile) {
     };
     relax_rows();
     for (int k = 1; k < a.K; ++k) {
-        T(*e)[6][64] = edge[k & 1];
+        T(*e)[6][64] = edge[k % NB];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             e[wave][q][lane] = f[0][q];                // to the row below the first

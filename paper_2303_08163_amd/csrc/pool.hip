@@ -196,7 +196,19 @@ static T2Geom t2_geom(int64_t nx, int64_t ny, int dtype, int R, bool persistent)
 
 // Whether a class's launches of two steps take blocks (k_pool_block2) instead
 // of the sweeps above.
+constexpr int64_t kPoolBlockNodes = 4096;  // least nodes of a class's two-step slots
 static bool t2_blocks(const lbm_pool_tuning &t) { return !t.persistent && t.time_rows == 0; }
+
+// Beyond the last-level cache fewer workgroups per compute unit keep fewer HBM pages
+// open: block launches then ask for LDS that they do not use, so that three
+// (FP32) or two (FP64) fit instead of four (us per step, four / limited: 9.9M nodes
+// FP32 80.4 / 78.5, FP64 164.7 / 151.7; within the cache 1.1M FP64 13.8 / 15.3).
+constexpr size_t kPoolCacheBytes = (size_t)256 << 20, kPoolBlockPad = 30000;
+// Every second launch takes its blocks in reverse order: it starts with what the
+// one before left in the cache (us per step, forward / alternating: FP32 4.9M nodes 41.1 /
+// 39.0, 6.7M 55.7 / 51.8, 9.9M 80.6 / 78.5, FP64 2.9M 47.5 / 44.5; nothing is gained
+// beyond three times the cache: FP64 9.9M 151.7 / 153.6).
+constexpr size_t kPoolBackBytes = 3 * kPoolCacheBytes;
 
 // Slots that the tile-ordered persistent form may advance (D2Q9, FP64 or FP32
 // deviation storage, row-interleaved layout, persistent two-step tuning) carry
@@ -612,10 +624,14 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
         const int cdim = c >= 8 ? 3 : 2, cdtype = (c % 8) / 2;
         const bool corr = (c & 1) != 0;
         // two steps per launch: D2Q9 FP64 / FP32_DEV row-interleaved slots, when those
-        // taking at least two steps hold as many nodes as a single domain needs for
-        // two steps per launch to pay (2048^2 FP32, 1024^2 FP64; a workgroup sweeps its
-        // rows one after another): with a few small slots the one-step form answers
-        // sooner (served p50 latency 44 against 18 ms)
+        // taking at least two steps hold enough nodes.  Blocks pay at any number (us per
+        // step, one step per launch / blocks: 15k nodes FP32 3.91 / 2.70, 73k 4.37 / 2.80,
+        // 273k 7.18 / 4.61, 1.1M 14.99 / 10.20, 2.9M 32.2 / 21.4; FP64 15k 4.13 / 2.86, 273k
+        // 9.47 / 5.15); the smallest classes keep the launch count of one step per
+        // launch.  Sweeps need what a single domain needs for them (2048^2 FP32,
+        // 1024^2 FP64; a workgroup sweeps its rows one after another): with a few
+        // small slots the one-step form answers sooner (served p50 latency 44 against
+        // 18 ms)
         bool two = p->tun.time_block == 2 && cdim == 2 && (cdtype == kF64 || cdtype == kDevF64) &&
                    p->tun.layout == LBM_LAYOUT_ROWS;
         size_t class_buf_bytes = 0;
@@ -625,7 +641,9 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
             if (steps_of(i) >= 2)
                 two_nodes += p->slots[i].d.L.n;
         }
-        two = two && two_nodes >= (cdtype == kF64 ? (int64_t)1 << 20 : (int64_t)1 << 22);
+        two = two && two_nodes >= (t2_blocks(p->tun) ? kPoolBlockNodes
+                                   : cdtype == kF64  ? (int64_t)1 << 20
+                                                     : (int64_t)1 << 22);
         const bool pers = p->tun.persistent != 0;
         const int B = t2_block(cdtype, pers), TX = t2_cols(cdtype, pers);
         const int R = t2_rows(p->tun, cdtype);
@@ -777,7 +795,8 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
                 fn2 = dtype == kF64 ? (corr ? k_pool_block2<kF64, true> : k_pool_block2<kF64, false>)
                                     : (corr ? k_pool_block2<kDevF64, true> : k_pool_block2<kDevF64, false>);
             const dim3 block2((unsigned)(blocks ? 64 * kPoolBlockWaves : B));
-            const size_t lds2 = blocks ? 0 : lds;
+            const bool beyond_cache = 2 * class_buf_bytes > kPoolCacheBytes;
+            const size_t lds2 = blocks ? (beyond_cache ? kPoolBlockPad : 0) : lds;
             PoolStepFn fn1 = pool_kernel<2>(dtype, corr, false);
             // the larger LDS need of the two tile forms (whole-row: the most sub-tiles)
             PoolRunArgs a2 = a;
@@ -816,6 +835,7 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
             };
             for (int64_t L = 0; !df && 2 * L + 1 <= smax; ++L) {
                 a2.step0 = (int)L;
+                a2.back = 2 * class_buf_bytes <= kPoolBackBytes && (L & 1) != 0;
                 a2.nsteps = 2;
                 // two-step tiles of the slots with s_j >= 2 L + 2: a prefix of each part
                 const int p1 = count_ge(0, nw, 2 * L + 2), p2 = count_ge(nw, n, 2 * L + 2);

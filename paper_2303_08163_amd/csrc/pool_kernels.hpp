@@ -52,6 +52,7 @@ struct PoolRunArgs {
     const int *tile_start;    // n + 1 running tile counts, tile_start[0] = 0
     const int64_t *remaining; // n remaining step counts at the start of the run
     int n;
+    int back;                 // k_pool_block2: walk the tiles in reverse order
     int step0;                // first step of this launch within the run
     int nsteps;               // steps done by this launch
     unsigned *barrier;        // persistent form: arrival counter, zero at launch
@@ -173,14 +174,15 @@ __global__ __launch_bounds__(1024) void k_pool_step2(PoolRunArgs a) {
 // rows each, two of them halo rows, like the outer two columns.  A block reads
 // its rows at once where the sweeps read them one after another between
 // barriers.  us per step, sweeps of 16 rows / blocks: 64 domains of 32..512 (4.9M
-// nodes) FP32 48.9 / 42.2, FP64 80.5 / 76.1; 512 such 326 / 314 and 570 / 569; 24 of
-// 500..1024 FP32 129 / 117.  Bound by HBM, at 4.2 TB/s of one read and one
-// write; eight wavefronts of two rows beat four to twelve of one, two or four
-// by 1-20 %.
+// nodes) FP32 48.9 / 39.0, FP64 80.5 / 76.1; 512 such 326 / 307 and 570 / 569; 24 of
+// 500..1024 FP32 129 / 113.  Bound by HBM, at 4.5 TB/s of one read and one
+// write, with the vector units busy for 55 %; eight wavefronts of two rows beat
+// four to twelve of one, two or four by 1-20 %, and a workgroup that loads its
+// next block during the steps of one (FP32 4.9M 42.2) ran slower.
 constexpr int kPoolBlockWaves = 8, kPoolBlockRows = 2 * kPoolBlockWaves - 2, kPoolBlockCols = 62;
 template <int DT, bool CORR>
 __global__ __launch_bounds__(64 * kPoolBlockWaves) void k_pool_block2(PoolRunArgs a) {
-    const int t = xcd_tile((int)blockIdx.x, (int)gridDim.x) + a.tile_base;
+    const int t = xcd_tile((int)blockIdx.x, (int)gridDim.x, a.back != 0) + a.tile_base;
     int lo = 0, hi = a.n - 1;  // last slot k with tile_start[k] <= t
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(64 * kPoolBlockWaves) void k_pool_block2(PoolRunArg
     const int nx = dd.nx, p = (dd.parity + a.step0) & 1;
     const BlockArgs b{dd.buf[p], dd.buf[p ^ 1], nx, dd.ny, 2, kPoolBlockCols, kPoolBlockRows,
                       (nx + kPoolBlockCols - 1) / kPoolBlockCols, dd.ps, dd.rs, dd.relax, dd.flag};
-    block2_tile<DT, CORR, kEqEntropic, 2>(b, t - a.tile_start[lo]);
+    block2_tile<DT, CORR, kEqEntropic, 2, kPoolBlockWaves, 1>(b, t - a.tile_start[lo]);
 }
 
 // One step (a.step0) over the tiles [tile_base, tile_base + grid): the active
