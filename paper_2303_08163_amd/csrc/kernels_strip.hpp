@@ -489,7 +489,7 @@ __global__ __launch_bounds__(ONE ? 64 : kRowMax) void k_row1(RowArgs a) {
                 for (int w = 1; w < 4; ++w)
                     part[b] += 4 * b + w < waves ? sums[slot][4 * b + w] : 0.0;
             }
-            *out = (part[0] + part[2]) + (part[1] + part[3]);
+            *out = (part[0] + part[1]) + (part[2] + part[3]);
         }
         ++out;
     };

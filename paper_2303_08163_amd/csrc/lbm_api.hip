@@ -349,7 +349,10 @@ int validate_config(const lbm_config *cfg, const lbm_tuning *tun, Layout *out) {
         plan2(cfg, L);
     else if (automatic)
         plan3(cfg, L);
-    L.red_blocks = (int)std::min<int64_t>(1024, (L.n + kReduceThreads - 1) / kReduceThreads);
+    // workgroups of the reductions: each arrival at the counter takes about 10 ns, so no
+    // more than keep the loads busy (moments FP32, us at 1024 / 512 / 256: 512^2 20.2 /
+    // 13.0 / 10.3, 1024^2 24.8 / 19.0 / 19.6, 4096^2 193 / 181 / 268)
+    L.red_blocks = (int)std::min<int64_t>(L.n <= (1 << 18) ? 256 : 512, (L.n + kReduceThreads - 1) / kReduceThreads);
     // workspace: buffer A | buffer B | flag block (256 B) | diag out (256 B) | partials
     L.off_buf[0] = 0;
     L.off_buf[1] = round_up(L.buf_bytes, 256);
