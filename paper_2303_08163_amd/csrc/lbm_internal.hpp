@@ -103,7 +103,7 @@ int launch_block2(const Layout &L, const StepArgs &args, int dtype, bool corr, i
 constexpr size_t kSweep3Bytes = (size_t)96 << 20;  // sweeps: both population buffers from here on
 constexpr int64_t kBlock3Nodes = 200000;           // blocks: domains up to here
 void plan3(const lbm_config *cfg, Layout &L);
-int launch_sweep3(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
+int launch_sweep3(const Layout &L, const StepArgs &args, int dtype, bool corr, bool back, hipStream_t s);
 int launch_block3(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
 
 // Bind a domain to its workspace and enqueue f = f^eq(rho, u) plus the flag

@@ -117,21 +117,22 @@ void plan3(const lbm_config *cfg, Layout &L) {
 }
 
 template <int DT, int EQ, bool CORR>
-static void (*sweep3_w(int w))(Sweep3Args) {
-    return w == 66 ? k_sweep3<DT, CORR, EQ, 66> : k_sweep3<DT, CORR, EQ, 34>;
+static void (*sweep3_w(int w, bool back))(Sweep3Args) {
+    return back ? (w == 66 ? k_sweep3<DT, CORR, EQ, 66, true> : k_sweep3<DT, CORR, EQ, 34, true>)
+                : (w == 66 ? k_sweep3<DT, CORR, EQ, 66, false> : k_sweep3<DT, CORR, EQ, 34, false>);
 }
 template <int DT, int EQ>
-static void (*sweep3_corr(bool corr, int w))(Sweep3Args) {
-    return corr ? sweep3_w<DT, EQ, true>(w) : sweep3_w<DT, EQ, false>(w);
+static void (*sweep3_corr(bool corr, int w, bool back))(Sweep3Args) {
+    return corr ? sweep3_w<DT, EQ, true>(w, back) : sweep3_w<DT, EQ, false>(w, back);
 }
 template <int DT>
-static void (*sweep3_kernel(int eq, bool corr, int w))(Sweep3Args) {
-    return eq == LBM_EQ_POLY2     ? sweep3_corr<DT, kEqPoly2>(corr, w)
-           : eq == LBM_EQ_PRODUCT ? sweep3_corr<DT, kEqProduct>(corr, w)
-                                  : sweep3_corr<DT, kEqEntropic>(corr, w);
+static void (*sweep3_kernel(int eq, bool corr, int w, bool back))(Sweep3Args) {
+    return eq == LBM_EQ_POLY2     ? sweep3_corr<DT, kEqPoly2>(corr, w, back)
+           : eq == LBM_EQ_PRODUCT ? sweep3_corr<DT, kEqProduct>(corr, w, back)
+                                  : sweep3_corr<DT, kEqEntropic>(corr, w, back);
 }
 
-int launch_sweep3(const Layout &L, const StepArgs &s, int dtype, bool corr, hipStream_t stream) {
+int launch_sweep3(const Layout &L, const StepArgs &s, int dtype, bool corr, bool back, hipStream_t stream) {
     const Sweep3Geom &g = L.sweep3;
     Sweep3Args a{};
     a.src = s.src;
@@ -147,8 +148,8 @@ int launch_sweep3(const Layout &L, const StepArgs &s, int dtype, bool corr, hipS
     a.rs = L.rs;
     a.relax = s.relax;
     a.flag = s.flag;
-    void (*fn)(Sweep3Args) = dtype == kF64 ? sweep3_kernel<kF64>(L.eq, corr, g.w)
-                                           : sweep3_kernel<kDevF64>(L.eq, corr, g.w);
+    void (*fn)(Sweep3Args) = dtype == kF64 ? sweep3_kernel<kF64>(L.eq, corr, g.w, back)
+                                           : sweep3_kernel<kDevF64>(L.eq, corr, g.w, back);
     const int64_t wgs = (int64_t)a.tiles_x * a.tiles_y * ((s.nz + g.planes - 1) / g.planes);
     const unsigned threads = (unsigned)((g.w * (g.rows + 2) + 63) / 64 * 64);
     hipLaunchKernelGGL(fn, dim3((unsigned)wgs), dim3(threads), 0, stream, a);
