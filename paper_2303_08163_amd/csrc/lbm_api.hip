@@ -833,7 +833,7 @@ static int enqueue_deep(lbm_handle *h, int cur, int K, hipStream_t s) {
     return d.L.row == 1   ? launch_row1(d.L, a, d.cfg.dtype, corr, K, nullptr, s)
            : d.L.dim == 1 ? launch_strip1(d.L, a, d.cfg.dtype, corr, K, s)
            : d.L.block2.rpt ? launch_block2(d.L, a, d.cfg.dtype, corr, K, s)
-           : d.L.dim == 2 ? launch_strip2(d.L, a, d.cfg.dtype, corr, K, s)
+           : d.L.dim == 2 ? launch_strip2(d.L, a, d.cfg.dtype, corr, K, cur != 0, s)
            : d.L.block3.own_x ? launch_block3(d.L, a, d.cfg.dtype, corr, s)
                           : launch_sweep3(d.L, a, d.cfg.dtype, corr, cur != 0, s);
 }

@@ -95,7 +95,7 @@ struct RowEnergy {
 int row1_plan(int64_t nx);
 int launch_row1(const Layout &L, const StepArgs &args, int dtype, bool corr, int steps, const RowEnergy *e,
                 hipStream_t s);
-int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
+int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, bool back, hipStream_t s);
 
 int launch_block2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, hipStream_t s);
 

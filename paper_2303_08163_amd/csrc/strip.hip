@@ -99,19 +99,23 @@ void plan2(const lbm_config *cfg, Layout &L) {
     }
 }
 
-template <int DT, int K, int EQ>
+template <int DT, int K, int EQ, bool BACK>
 static void (*strip2_corr(bool corr))(StripArgs) {
     constexpr int W = strip2_occupancy(DT, K);
-    return corr ? k_strip2<DT, true, EQ, K, W> : k_strip2<DT, false, EQ, K, W>;
+    return corr ? k_strip2<DT, true, EQ, K, W, BACK> : k_strip2<DT, false, EQ, K, W, BACK>;
+}
+template <int DT, int K, bool BACK>
+static void (*strip2_eq(int eq, bool corr))(StripArgs) {
+    return eq == LBM_EQ_POLY2     ? strip2_corr<DT, K, kEqPoly2, BACK>(corr)
+           : eq == LBM_EQ_PRODUCT ? strip2_corr<DT, K, kEqProduct, BACK>(corr)
+                                  : strip2_corr<DT, K, kEqEntropic, BACK>(corr);
 }
 template <int DT, int K>
-static void (*strip2_kernel(int eq, bool corr))(StripArgs) {
-    return eq == LBM_EQ_POLY2     ? strip2_corr<DT, K, kEqPoly2>(corr)
-           : eq == LBM_EQ_PRODUCT ? strip2_corr<DT, K, kEqProduct>(corr)
-                                  : strip2_corr<DT, K, kEqEntropic>(corr);
+static void (*strip2_kernel(int eq, bool corr, bool back))(StripArgs) {
+    return back ? strip2_eq<DT, K, true>(eq, corr) : strip2_eq<DT, K, false>(eq, corr);
 }
 
-int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int K, hipStream_t stream) {
+int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int K, bool back, hipStream_t stream) {
     StripArgs a{};
     a.src = s.src;
     a.dst = s.dst;
@@ -127,9 +131,9 @@ int launch_strip2(const Layout &L, const StepArgs &s, int dtype, bool corr, int 
     a.rs = L.rs;
     a.relax = s.relax;
     a.flag = s.flag;
-    void (*fn)(StripArgs) = dtype == kF64 ? (K == 6 ? strip2_kernel<kF64, 6>(L.eq, corr)
-                                                    : strip2_kernel<kF64, 4>(L.eq, corr))
-                                          : strip2_kernel<kDevF64, 4>(L.eq, corr);
+    void (*fn)(StripArgs) = dtype == kF64 ? (K == 6 ? strip2_kernel<kF64, 6>(L.eq, corr, back)
+                                                    : strip2_kernel<kF64, 4>(L.eq, corr, back))
+                                          : strip2_kernel<kDevF64, 4>(L.eq, corr, back);
     const int64_t waves = (int64_t)a.strips * a.chunks;
     constexpr int per_wg = kStripThreads / 64;
     hipLaunchKernelGGL(fn, dim3((unsigned)((waves + per_wg - 1) / per_wg)), dim3(kStripThreads), 0, stream, a);
