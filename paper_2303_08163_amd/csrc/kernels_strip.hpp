@@ -230,10 +230,11 @@ __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(W
 // K - 1 halo columns and rows on each side and 64 - 2 (K - 1) own columns.
 //
 // Bound: the gap between launches (2.6 us) and the latency of a step's chain of
-// FP64 operations, about 1.2 us per four steps for each row a SIMD holds; one
-// step per launch paid the gap every step (us per step, before / after: 64^2
-// FP64 2.84 / 1.20, 200 x 150 3.03 / 1.46, 300^2 4.50 / 1.86, 500 x 333 FP32 with the
-// correction 4.23 / 2.61).
+// FP64 operations, about 0.27 us for each row a SIMD collides; rows that no later
+// step needs are left out.  One step per launch paid the gap every step (us per
+// step, one step per launch / five: 64^2 FP64 2.84 / 1.10, 200 x 150 3.03 / 1.30, 300^2
+// 4.50 / 1.64, 500 x 333 FP32 with the correction 4.23 / 2.24; four steps with every
+// row to the end 1.29, 1.59, 2.00 and 2.84).
 struct BlockArgs {
     const void *src;  // f*(t), row-interleaved layout
     void *dst;        // f*(t + K)
@@ -285,15 +286,17 @@ __device__ __forceinline__ void block2_tile(const BlockArgs &a, int tile) {
     // own rows and columns; the domain flag is taken from them at every step
     const bool own_col = lane >= h && lane < h + a.own_x && x0 + lane - h < nx;
     bool bad = false;
-    auto relax_rows = [&] {
+    // `halo` rows on each side are still needed (uniform; the others' values are unused)
+    auto relax_rows = [&](int halo) {
 #pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-            const bool b = collide_dt<2, DT, CORR, EQ>(f[j], a.relax);
-            const bool own_row = r0 + j >= 0 && r0 + j < a.own_y && y0 + r0 + j < ny;  // uniform
-            bad |= b && own_row;
-        }
+        for (int j = 0; j < RPT; ++j)
+            if (r0 + j >= -halo && r0 + j < a.own_y + halo) {
+                const bool b = collide_dt<2, DT, CORR, EQ>(f[j], a.relax);
+                const bool own_row = r0 + j >= 0 && r0 + j < a.own_y && y0 + r0 + j < ny;
+                bad |= b && own_row;
+            }
     };
-    relax_rows();
+    relax_rows(h);
     for (int k = 1; k < a.K; ++k) {
         T(*e)[6][64] = edge[k % NB];
 #pragma unroll
@@ -325,7 +328,7 @@ __device__ __forceinline__ void block2_tile(const BlockArgs &a, int tile) {
 #pragma unroll
             for (int i = 0; i < 9; ++i)
                 f[j][i] = g[j][i];
-        relax_rows();
+        relax_rows(h - k);
     }
     raise_flag(a.flag, bad && own_col);
     if (!own_col)

@@ -659,12 +659,16 @@ int domain_energy(DomainState &d, hipStream_t s, const double *U, double rho_ref
 
 using namespace lbm;
 
-// Steps of small domains are bound by the host's launch rate (about 3 us per
-// launch), so long runs replay a captured HIP graph of kGraphSteps launches
-// instead.  kGraphSteps is even: the population buffers are back in place
-// after each replay, so one graph per starting buffer serves every call.  The
-// graph holds the same kernels with the same arguments, so results are
-// bitwise those of plain launches.
+// One-step launches of small domains are bound by the host's launch rate (about
+// 3 us per launch), so long runs replay a captured HIP graph of kGraphSteps steps
+// instead.  A replay leaves the population buffers where they were, so one graph
+// per starting buffer serves every call.  The graph holds the same kernels with
+// the same arguments, so results are bitwise those of plain launches.
+// Launches of several steps outlast the host's part, and follow one another sooner
+// plainly than inside a graph, which also cuts runs into 32 steps (us per step, graph /
+// plain: D1Q3 3000 nodes FP32 0.54 / 0.37, D2Q9 64^2 FP64 1.19 / 1.10, 2048^2 FP64
+// 27.9 / 24.5; one step per launch 700 nodes 2.2 / 2.7), so D1Q3 and D2Q9 have no graph
+// then; D3Q27, where the two are within 2 %, keeps it.
 constexpr int kGraphSteps = 32;
 
 struct lbm_handle {
@@ -673,7 +677,7 @@ struct lbm_handle {
     hipStream_t capture = nullptr;            // private stream the graphs are captured on
     hipGraph_t graph[2] = {nullptr, nullptr};  // by the buffer holding the state at the start
     hipGraphExec_t exec[2] = {nullptr, nullptr};
-    bool graphs_off = false;                   // a graph call failed once: plain launches only
+    bool graphs_off = false;                   // plain launches only: several steps each, or a graph call failed
     double *host = nullptr;                    // pinned: results of lbm_moments (NULL: none could be had)
 };
 
@@ -793,6 +797,7 @@ int lbm_create_tuned(const lbm_config *cfg, const lbm_tuning *tuning, void *work
         h->host = nullptr;
     }
     // capture the step graphs now, so that no later call pays for it
+    h->graphs_off = L.deep != 0 && L.dim < 3;
     if (!L.zhalo) {
         prepare_step_graphs(h);
     }
@@ -861,8 +866,8 @@ static int enqueue_steps(lbm_handle *h, int cur, int K, hipStream_t s) {
     return enqueue_deep(h, cur, K, s);
 }
 
-// Launches of a graph of kGraphSteps steps (even for every time_block and
-// strip length: the population buffers are back in place after a replay).
+// Launches of a graph of kGraphSteps steps (an odd number would leave the state in
+// the other buffer).
 static int graph_launches(const Layout &L) {
     int launches = 0;
     for (int64_t n = kGraphSteps; n > 0; n -= next_steps(L, n))

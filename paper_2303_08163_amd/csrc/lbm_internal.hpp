@@ -78,7 +78,6 @@ int launch_step(const Layout &L, const StepArgs &args, int dtype, bool corr, hip
 int launch_step2(const Layout &L, const StepArgs &args, int dtype, bool corr, hipStream_t s);
 
 // Launches with the intermediate states in registers (strip.hip).
-constexpr int kBlock2Steps = 4;           // steps per launch of D2Q9 blocks
 constexpr int64_t kStrip1Wide = 1 << 22;  // D1Q3 rows with many columns per lane
 void plan2(const lbm_config *cfg, Layout &L);
 int strip1_steps(int64_t nx);

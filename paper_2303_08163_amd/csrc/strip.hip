@@ -42,15 +42,28 @@ static int strip2_rows(int64_t nx, int64_t ny, int dtype, int K, double *us) {
     return (int)((ny + best_c - 1) / best_c);
 }
 
-// Tiling of k_block2 for four steps per launch: rows per wavefront and wavefronts
-// with the least estimated time, and that time in us per launch.  A compute
-// unit that holds q rows of wavefronts on each SIMD takes about 1.25 q us for the
-// four steps (64^2, one wavefront row each, 8 wavefronts: 4.8 us with the launch;
-// 12: 6.1; 300^2 16: 7.7; two rows each, 8: 7.9; 512^2, two such workgroups per
-// compute unit: 13.0).
-static Block2Geom block2_geom(int64_t nx, int64_t ny, double *us) {
+// Rows that the busiest SIMD of a k_block2 workgroup collides in K steps: the
+// halo shrinks by a row on each side every step, wavefront w runs on SIMD w mod 4.
+static int block2_rows(int K, int rpt, int waves, int own) {
+    int sum = 0;
+    for (int halo = K - 1; halo >= 0; --halo) {
+        int rows[4] = {0, 0, 0, 0};
+        for (int r = 0; r < waves * rpt; ++r)
+            if (r - (K - 1) >= -halo && r - (K - 1) < own + halo)
+                ++rows[r / rpt % 4];
+        sum += std::max(std::max(rows[0], rows[1]), std::max(rows[2], rows[3]));
+    }
+    return sum;
+}
+
+// Tiling of k_block2 for K steps per launch: rows per wavefront and wavefronts
+// with the least estimated time, and that time in us per launch.  Fitted to 182
+// tilings of 64^2 to 512^2 that run in one round: 3.15 us, 0.115 for every step
+// and 0.27 for every row that a SIMD collides, within 0.6 us; several workgroups
+// per compute unit take 1.1 times their sum.
+static Block2Geom block2_geom(int64_t nx, int64_t ny, int K, double *us) {
     Block2Geom g{};
-    constexpr int K = kBlock2Steps, own = 64 - 2 * (K - 1);
+    const int own = 64 - 2 * (K - 1);
     const int64_t tiles_x = (nx + own - 1) / own;
     *us = -1.0;
     for (int rpt : {1, 2})
@@ -58,9 +71,10 @@ static Block2Geom block2_geom(int64_t nx, int64_t ny, double *us) {
             const int rows = waves * rpt - 2 * (K - 1);
             if (rows < 1)
                 continue;
-            const int64_t tiles_y = (ny + rows - 1) / rows, wgs = tiles_x * tiles_y;
+            const int64_t tiles_y = (ny + rows - 1) / rows, wgs = tiles_x * tiles_y, q = (wgs + 255) / 256;
+            const int own_y = (int)((ny + tiles_y - 1) / tiles_y);
             const double t =
-                kLaunchUs + 1.25 * (double)((wgs + 255) / 256) * (double)((waves + 3) / 4 * rpt);
+                3.15 + 0.115 * K + 0.27 * (q > 1 ? 1.1 * (double)q : 1.0) * block2_rows(K, rpt, waves, own_y);
             if (*us < 0.0 || t < *us - 1e-9 || (t < *us + 1e-9 && wgs < (int64_t)g.tiles_x * g.tiles_y)) {
                 *us = t;
                 g.rpt = rpt;
@@ -75,12 +89,14 @@ static Block2Geom block2_geom(int64_t nx, int64_t ny, double *us) {
 }
 
 // Which form the runs of a D2Q9 domain take: strips of 4 steps per launch (FP32)
-// or 6 and 4 (FP64), blocks of 4, by the estimated time per step, or neither.
+// or 6 and 4 (FP64), blocks of 5 or 4, by the estimated time per step, or neither.
 // FP32 strips are bound by the FP64 arithmetic at 4 steps already (4096^2, us
 // per step: 3 steps 101.5, 4 steps 89.6, 6 steps 98.4 with one wavefront per
 // SIMD less); FP64 by HBM until 6 (4 steps 131.8, 5 112.6, 6 96.6, 8 118.6 with
-// one wavefront per SIMD).  Blocks win below about 600^2 (us per step, FP64 blocks /
-// strips: 512^2 3.3 / 4.2, 700 x 600 5.0 / 5.1, 1024^2 9.2 / 8.3).
+// one wavefront per SIMD).  Blocks are best with 5 steps (us per step, FP64 3 / 4 / 5 /
+// 6 / 8 steps: 64^2 - / 1.25 / 1.13 / 1.23 / 1.22, 300^2 1.95 / 1.87 / 1.65 / 1.94 /
+// 1.83), FP32 with several per compute unit 4 (512^2 3.35, 5 steps 3.43).  They win below about 700^2 (us per step, FP64 blocks /
+// strips: 512^2 3.2 / 4.2, 700 x 600 3.9 / 5.1; 1024^2 with four steps 9.2 / 8.3).
 void plan2(const lbm_config *cfg, Layout &L) {
     if (L.dim != 2 || L.layout != LBM_LAYOUT_ROWS || (cfg->dtype != LBM_FP64 && cfg->dtype != LBM_FP32_DEV))
         return;
@@ -90,10 +106,13 @@ void plan2(const lbm_config *cfg, Layout &L) {
     const bool six = cfg->dtype == LBM_FP64;
     L.strip_rows[0] = strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 4, &us4);
     L.strip_rows[1] = six ? strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 6, &us6) : 0;
-    const Block2Geom g = block2_geom(cfg->nx, cfg->ny, &usb);
-    if (L.tblock == 1 && usb / kBlock2Steps < (six ? us6 / 6 : us4 / 4)) {
+    int K = 5;
+    Block2Geom g = block2_geom(cfg->nx, cfg->ny, K, &usb);
+    if (!six && (int64_t)g.tiles_x * g.tiles_y > 256)
+        g = block2_geom(cfg->nx, cfg->ny, K = 4, &usb);
+    if (L.tblock == 1 && usb / K < (six ? us6 / 6 : us4 / 4)) {
         L.block2 = g;
-        L.deep = kBlock2Steps;
+        L.deep = K;
     } else {
         L.deep = six ? 6 : 4;
     }
@@ -154,7 +173,7 @@ static void (*block2_kernel(int eq, bool corr))(BlockArgs) {
                                   : block2_corr<DT, kEqEntropic, RPT>(corr);
 }
 
-// K <= kBlock2Steps steps (fewer leave more halo than they need).
+// K <= L.deep steps (fewer leave more halo than they need).
 int launch_block2(const Layout &L, const StepArgs &s, int dtype, bool corr, int K, hipStream_t stream) {
     const Block2Geom &g = L.block2;
     const BlockArgs a{s.src, s.dst, s.nx, s.ny, K, g.own_x, g.own_y, g.tiles_x, L.ps, L.rs, s.relax, s.flag};

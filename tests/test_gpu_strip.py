@@ -77,6 +77,15 @@ BLOCK_CASES = [  # (ny, nx), dtype, correction, equilibrium, step chunks
     ((333, 500), "fp32_dev", True, "entropic", (6, 64)),
     ((300, 300), "fp64", False, "entropic", (7,)),
     ((512, 509), "fp64", True, "entropic", (11,)),
+    # five steps: 56 own columns and one off, every remainder, rows the later steps leave out
+    ((64, 64), "fp64", True, "entropic", (5, 6, 7, 8, 9, 105)),
+    ((2, 56), "fp32_dev", False, "entropic", (10, 4)),
+    ((9, 57), "fp64", False, "product", (15,)),
+    ((17, 113), "fp32_dev", True, "poly2", (11, 3)),
+    ((41, 167), "fp64", True, "entropic", (10, 2)),
+    ((640, 601), "fp64", False, "entropic", (5, 9)),
+    # several workgroups per compute unit: four steps with float storage
+    ((509, 512), "fp32_dev", False, "entropic", (9, 2)),
 ]
 
 
