@@ -77,14 +77,18 @@ class RadiusEvaluator:
         # pinned staging, so that enqueueing a call does not wait for the stream
         self.host_states = torch.empty((n_states, 3), dtype=torch.float64, pin_memory=True)
         self.states = torch.empty((n_states, 3), dtype=torch.float64, device=self.device)
-        self.rmax = torch.empty(n_states, dtype=torch.float64, device=self.device)
+        # the radii and, in the word behind them, the unconverged count: one copy into
+        # pinned memory and one wait bring both back
+        self.out = torch.zeros(n_states + 1, dtype=torch.float64, device=self.device)
+        self.host_out = torch.empty(n_states + 1, dtype=torch.float64, pin_memory=True)
+        self.rmax = self.out[:n_states]
+        self.unconverged = self.out[n_states:].view(torch.int32)[:1]
         self.scratch = torch.empty(n_states, dtype=torch.int64, device=self.device)
-        self.unconverged = torch.zeros(1, dtype=torch.int32, device=self.device)
         # a stream of its own (default priority): the calls of evaluators run in
         # lockstep overlap on the GPU, one kernel's last wavefronts beside the
         # next one's first
         self.stream = torch.cuda.Stream(device=self.device)
-        for t in (self.states, self.rmax, self.scratch, self.unconverged):
+        for t in (self.states, self.out, self.scratch):
             t.record_stream(self.stream)  # not reused before that stream's work is done
         self.matrices = 0
         self.n = 0
@@ -109,9 +113,10 @@ class RadiusEvaluator:
         """(max radius (n,), unconverged count) of the last launch; waits for it."""
         import torch
         with torch.cuda.stream(self.stream):
-            r = self.rmax[:self.n].cpu().numpy()  # waits for the evaluator's stream
-            bad = int(self.unconverged.item())
-        return r, bad
+            self.host_out.copy_(self.out, non_blocking=True)
+        self.stream.synchronize()
+        host = self.host_out.numpy()
+        return host[:self.n].copy(), int(host[self.capacity:].view(np.int32)[0])
 
     def __call__(self, states: np.ndarray):
         """states (n, 3): tau, u_x, u_y.  Returns (max radius (n,), unconverged count)."""
