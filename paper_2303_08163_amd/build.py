@@ -9,6 +9,8 @@ from __future__ import annotations
 import glob
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -25,18 +27,28 @@ def sources():
 
 
 def build(verbose: bool = False) -> str:
+    """Compile every source (side by side) and link them."""
     tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(HERE, "csrc"),
-           *sources(), "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    noise = "is not a recognized feature for this target"
-    err = "\n".join(l for l in r.stderr.splitlines() if noise not in l and l.strip() != "1 warning generated.")
-    if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({r.returncode}):\n{err}")
-    if verbose and err.strip():
-        print(err)
+
+    def hipcc(args):
+        cmd = [HIPCC, *args]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        noise = "is not a recognized feature for this target"
+        err = "\n".join(l for l in r.stderr.splitlines() if noise not in l and l.strip() != "1 warning generated.")
+        if r.returncode != 0:
+            raise RuntimeError(f"hipcc failed ({r.returncode}):\n{err}")
+        if verbose and err.strip():
+            print(err)
+
+    with tempfile.TemporaryDirectory() as d:
+        objects = [os.path.join(d, os.path.basename(s) + ".o") for s in sources()]
+        flags = [f for f in FLAGS if f != "-shared"] + ["-I" + os.path.join(ROOT, "include"),
+                                                        "-I" + os.path.join(HERE, "csrc")]
+        with ThreadPoolExecutor(len(objects)) as pool:
+            list(pool.map(lambda so: hipcc([*flags, "-c", so[0], "-o", so[1]]), zip(sources(), objects)))
+        hipcc(["--offload-arch=gfx950", "-shared", "-fPIC", *objects, "-o", tmp])
     os.replace(tmp, LIB)
     return LIB
 
