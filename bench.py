@@ -4,11 +4,12 @@ LBGK on one MI355X.
 Headline workload: D3Q27, 256^3 periodic Taylor-Green vortex (u0 = 0.05,
 tau = 0.5005), populations stored in FP32 as deviations f_i - w_i rho0, all
 arithmetic in FP64, bulk correction off.  One "step" is one time step of the
-whole domain (one kernel launch).  Inputs are resident in HBM before timing.
+whole domain (a launch takes two).  Inputs are resident in HBM before timing.
 
 Prints ONE JSON line: MLUPS (= nodes * steps / s / 1e6), the roofline of the
-stream-collide kernel (algorithmic bytes 2 * Q * 4 = 216 B per node update,
-against the 8 TB/s HBM peak), and the CPU oracle timed on a bounded sample.
+stream-collide kernel (one read and one write of every population per launch,
+2 * Q * 4 = 216 B per node and launch, 108 B per node update, against the 8 TB/s
+HBM peak), and the CPU oracle timed on a bounded sample.
 """
 from __future__ import annotations
 
@@ -25,8 +26,19 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+# steps per launch of the library's default runs on the grids timed here: D3Q27 256^3
+# (two-step sweeps), D2Q9 4096^2 (strips); lbm_get_launch_info describes the one-step
+# kernel that ends a run
+D2Q9_STEPS = {"fp32_dev": 4, "fp64": 6}
+
+
+def d3q27_steps(n: int) -> int:
+    """Sweeps and blocks take two; cubes between them one."""
+    return 2 if 2 * 27 * 4 * n ** 3 > 96 << 20 or n <= 48 else 1
+
+
 METRIC = "MLUPS & % HBM roofline (D3Q27 256³ FP32); batched solves/s, p99 latency"
-PROFILE_SUMMARY = os.path.join(ROOT, "profiles", "stream_collide_d3q27_fp32dev_256.md")
+PROFILE_SUMMARY = os.path.join(ROOT, "profiles", "sweep3_d3q27_fp32dev_256.md")
 
 
 def kernel_source_digest() -> str:
@@ -35,7 +47,7 @@ def kernel_source_digest() -> str:
     they are unchanged since the counters were taken."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2303_08163_amd", "csrc")
-    for fn in ("node.hpp", "kernels.hpp"):
+    for fn in ("node.hpp", "kernels.hpp", "kernels_sweep3.hpp"):
         with open(os.path.join(csrc, fn), "rb") as f:
             h.update(fn.encode() + b"\0" + f.read())
     return h.hexdigest()[:16]
@@ -403,8 +415,9 @@ def bench_oracle_timing(budget_s: float = 6.0) -> dict:
 
 def bench_variants(steps: int = 100, warmup: int = 10) -> dict:
     """Throughput of the other equilibria and of the correction on the headline
-    grid (D3Q27 256^3 Taylor-Green, FP32 deviation storage, default vector
-    kernel)."""
+    grid (D3Q27 256^3 Taylor-Green, FP32 deviation storage, the default two steps
+    per launch).  gbs / frac count the bytes a launch moves by algorithm: one read
+    and one write of every population."""
     import torch
 
     from paper_2303_08163_amd import lbm, workloads
@@ -434,12 +447,12 @@ def bench_variants(steps: int = 100, warmup: int = 10) -> dict:
     for eq in ("entropic", "poly2", "product"):
         for corr in (False, True):
             dom = lbm.Domain(rd, ud, 0.5005, dtype="fp32_dev", bulk_correction=corr, equilibrium=eq, stream=stream)
-            out[f"d3q27_256_fp32_{eq}{'_corrected' if corr else ''}"] = timed(dom, 256 ** 3, 216)
+            out[f"d3q27_256_fp32_{eq}{'_corrected' if corr else ''}"] = timed(dom, 256 ** 3, 216 / d3q27_steps(256))
             dom.close()
-    # full FP64 storage of the headline workload (432 B per node update)
+    # full FP64 storage of the headline workload (432 B per node and launch)
     for corr in (False, True):
         dom = lbm.Domain(rd, ud, 0.5005, dtype="fp64", bulk_correction=corr, stream=stream)
-        rec = timed(dom, 256 ** 3, 432)
+        rec = timed(dom, 256 ** 3, 432 / d3q27_steps(256))
         rec["kernel"] = dom.launch_info()
         out[f"d3q27_256_fp64_entropic{'_corrected' if corr else ''}"] = rec
         dom.close()
@@ -553,12 +566,12 @@ def bench_d1q3(steps: int = 200, warmup: int = 64) -> dict:
 
 def bench_d2q9(steps: int = 100, warmup: int = 200) -> dict:
     """The D2Q9 4096^2 double shear layer (tau 0.5001), FP32 deviations and FP64,
-    correction off and on, with the default two steps per launch and with one.
-    gbs / frac count the bytes each launch moves by algorithm: one read and
-    one write of every population per launch (2 Q s per node per launch, so
-    Q s per node update with two steps per launch); gbs_2Qs_per_update is the
-    rate at 2 Q s per node update, an equivalent figure for the two-step
-    kernel, not bytes it moves."""
+    correction off and on, with the default steps per launch (FP32 four, FP64 six),
+    two (the sweeps through LDS) and one.  gbs / frac count the bytes each launch
+    moves by algorithm: one read and one write of every population per launch
+    (2 Q s per node per launch); gbs_2Qs_per_update is the rate at 2 Q s per node
+    update, an equivalent figure for launches of several steps, not bytes they
+    move."""
     import torch
 
     from paper_2303_08163_amd import lbm, workloads
@@ -569,7 +582,8 @@ def bench_d2q9(steps: int = 100, warmup: int = 200) -> dict:
     out = {}
     for corr in (False, True):
         for dt, s in (("fp32_dev", 4), ("fp64", 8)):
-            for name, tun in (("two_steps_per_launch", None), ("one_step_per_launch", lbm.make_tuning(time_block=1))):
+            for name, tun in (("default", None), ("two_steps_per_launch", lbm.make_tuning(time_block=2)),
+                              ("one_step_per_launch", lbm.make_tuning(time_block=1))):
                 dom = lbm.Domain(r2, u2, 0.5001, dtype=dt, bulk_correction=corr, stream=stream, tuning=tun)
                 info = dom.launch_info()
                 dom.step(warmup)
@@ -586,15 +600,15 @@ def bench_d2q9(steps: int = 100, warmup: int = 200) -> dict:
                 dom.close()
                 sec = min(reps)
                 mlups = 4096 ** 2 / sec / 1e6
-                k = info["time_block"]
+                k = info["time_block"] if tun else D2Q9_STEPS[dt]
                 own = 2 * 9 * s * 4096 ** 2 / (k * sec) / 1e9  # bytes of one launch / its time
                 key = f"{dt}_{name}{'_corrected' if corr else ''}"
                 out[key] = {
                     "mlups": round(mlups, 1), "us_per_step": round(sec * 1e6, 1),
                     "us_per_step_reps": [round(v * 1e6, 1) for v in reps], "steps_per_launch": k,
-                    "kernel": info["kernel"], "gbs": round(own, 1), "frac": round(own / HBM_PEAK_GBS, 4),
+                    "kernel": info["kernel"] if tun else "k_strip2", "gbs": round(own, 1), "frac": round(own / HBM_PEAK_GBS, 4),
                     "gbs_2Qs_per_update": round(mlups * 1e6 * 2 * 9 * s / 1e9, 1), "domain_error": d["domain_error"]}
-                if k > 1:
+                if k == 2:
                     out[key]["roofline_valu"] = valu_roofline(f"d2q9_4096.{key}", k * sec)
     return {"workload": "D2Q9 4096^2 double shear layer, tau 0.5001", "steps": steps, "warmup_steps": warmup,
             "repetitions": 3, "statistic": "best of the repetitions", "results": out}
@@ -792,9 +806,9 @@ def main() -> int:
 
     sec = ms / 1e3
     mlups = nodes * args.steps / sec / 1e6
-    bytes_per_lup = 2 * 27 * 4
-    per_launch_s = sec / args.steps
-    achieved = bytes_per_lup * nodes / per_launch_s / 1e9
+    bytes_per_launch = 2 * 27 * 4  # per node
+    per_launch_s = d3q27_steps(n) * sec / args.steps
+    achieved = bytes_per_launch * nodes / per_launch_s / 1e9
     traffic = measured_traffic()
 
     ceiling = bench_ceiling(n) if "ceiling" in sections else None
@@ -824,10 +838,8 @@ def main() -> int:
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "kernel": f"k_stream_collide_vec<D3Q27, FP32 deviations/FP64 arithmetic, no correction, "
-                      f"{launch['nodes_per_thread']} nodes per thread, row wave {launch['row_wave']}, "
-                      f"row-interleaved layout>",
-            "bytes_per_node_update": bytes_per_lup,
+            "kernel": "k_sweep3<D3Q27, FP32 deviations/FP64 arithmetic, no correction>, two steps per launch",
+            "bytes_per_node_update": bytes_per_launch / d3q27_steps(n), "steps_per_launch": d3q27_steps(n),
             "launch_avg_ms": round(per_launch_s * 1e3, 5),
         },
         "launch": launch,

@@ -121,16 +121,18 @@ typedef struct lbm_tuning {
                                  1 for FP32 storage on D2Q9 */
     int32_t flags;            /* LBM_TUNE_* bits for the vector kernels; < 0 selects the default */
     int32_t layout;           /* LBM_LAYOUT_*; 0 = default (row-interleaved) */
-    int32_t time_block;       /* LBGK steps per launch, the intermediate states kept in LDS
+    int32_t time_block;       /* LBGK steps per launch, the intermediate states kept on chip
                                  (LBM_FP64 or LBM_FP32_DEV, any equilibrium, row-interleaved
                                  layout): 1 = one; 2 on D2Q9 with nx >= 64; 2, 4 or 8 on
                                  D1Q3 with nx >= 16.  Step counts that are not a multiple
                                  end with one-step launches of the kernel the other fields
                                  select.
-                                 0 = default: 2 for D2Q9 domains of >= 2048^2 nodes (FP32) or
-                                 1024^2 (FP64), 8 for D1Q3 where allowed, else 1 -- when
-                                 block_x, block_y, nodes_per_thread, flags and layout are
-                                 left at their defaults */
+                                 0 = default: the library's choice.  With block_x, block_y,
+                                 nodes_per_thread, flags and layout left at their defaults
+                                 and FP64 or FP32_DEV storage, launches take as many steps
+                                 as pay: D1Q3 8 or 16 (any number on rows of up to 512
+                                 nodes), D2Q9 4 to 6, D3Q27 2 where sweeps or blocks pay; the
+                                 results are bitwise those of 1 */
     int32_t time_rows;        /* time_block = 2: rows swept per workgroup (>= 1; 0 = default);
                                  must be 0 otherwise */
     int32_t reserved;         /* must be 0 */
@@ -193,11 +195,12 @@ int lbm_create_tuned(const lbm_config *cfg, const lbm_tuning *tuning, void *work
                      size_t ws_bytes, const double *rho, const double *u, void *stream,
                      lbm_handle **out);
 
-/* Enqueue nsteps time steps (one fused stream-and-collide kernel launch each)
- * on the handle's stream and return without synchronising.  Runs of 64 steps
- * or more replay a captured HIP graph of 32 launches (the same kernels and
- * arguments, so bitwise the same results) to relieve the host's launch rate;
- * the graphs are captured by lbm_create.  nsteps = 0 is a no-op.  Errors: LBM_EINVAL (h NULL, nsteps < 0, nsteps > 1 on a z-slab,
+/* Enqueue nsteps time steps (fused stream-and-collide kernel launches of one or
+ * several steps, see lbm_tuning.time_block) on the handle's stream and return
+ * without synchronising.  Where launches are short (one step each, and D3Q27),
+ * runs of 64 steps or more replay a captured HIP graph of 32 steps (the same
+ * kernels and arguments, so bitwise the same results) to relieve the host's launch
+ * rate; the graphs are captured by lbm_create.  nsteps = 0 is a no-op.  Errors: LBM_EINVAL (h NULL, nsteps < 0, nsteps > 1 on a z-slab,
  * which needs a halo exchange between steps); LBM_EDEVICE (launch failure). */
 int lbm_step(lbm_handle *h, int64_t nsteps);
 
@@ -272,14 +275,16 @@ int lbm_moments(lbm_handle *h, double *rho, double *u, lbm_diag *diag);
  * pointer to Q * N doubles.  Synchronises the stream. */
 int lbm_get_populations(lbm_handle *h, double *out);
 
-/* The launch the library chose for a domain's steps (from its configuration
- * and tuning), so that callers and tests can state which kernel ran. */
+/* The launch of time_block steps that a domain's configuration and tuning select,
+ * so that callers and tests can state it.  With the default tuning runs take
+ * longer launches where they pay (lbm_tuning.time_block = 0), and this one for what
+ * is left of a run. */
 enum {
     LBM_KERNEL_NODE = 1,      /* one node per thread (any nx) */
     LBM_KERNEL_VECTOR = 2,    /* nodes_per_thread consecutive x nodes per thread, one 16-byte
                                  load and store per population run, x shifts by lane rotation */
     LBM_KERNEL_TWO_STEP = 3,  /* D2Q9, two steps per launch, the intermediate state in LDS */
-    LBM_KERNEL_MULTI_STEP = 4 /* D1Q3, time_block steps per launch in LDS segments */
+    LBM_KERNEL_MULTI_STEP = 4 /* D1Q3, time_block steps per launch in registers */
 };
 typedef struct lbm_launch_info {
     int32_t kernel;           /* LBM_KERNEL_* of full launches (step counts that are not a multiple
@@ -419,7 +424,7 @@ typedef struct lbm_pool_tuning {
                            wavefront always stays within one row.  0: every slot uses
                            tile_x x tile_y.  Not with flat; other values are LBM_EINVAL */
     int32_t time_block; /* 2: D2Q9 classes (LBM_FP64 or LBM_FP32_DEV, row-interleaved slots)
-                           advance two steps per launch, the intermediate state in LDS, in
+                           advance two steps per launch, the intermediate state on chip, in
                            runs where the class's slots that take at least two steps hold
                            >= 4096 nodes; a slot whose step count in
                            the run is odd takes its last step in a one-step launch.  With

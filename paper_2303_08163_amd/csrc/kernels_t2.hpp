@@ -23,10 +23,9 @@
 // workgroup reads the populations of (tx + 2) x (rows + 2) step-1 node
 // updates and writes those of its tx x rows nodes once.
 //
-// A D3Q27 node holds 27 populations, so the ring would need (tx + 2) x 27 x 4
-// rows of a 2-D tile (and the x-y halo grows the re-read area); in 160 KB of
-// LDS that does not fit at any useful tile size, so D3Q27 stays one step per
-// launch.
+// These are the launches of time_block = 2 and of pools in sweeps; domains left to
+// the library take register strips or blocks (kernels_strip.hpp), D3Q27 ones the
+// sweeps and blocks of kernels_sweep3.hpp.
 #pragma once
 
 #include "kernels.hpp"
