@@ -439,8 +439,8 @@ __global__ __launch_bounds__(kStripThreads) void k_strip1(StripArgs a) {
 //
 // Bound: the dependence chain of one collision (one wavefront per SIMD up to
 // 256 nodes), 0.19 us per step within one wavefront, 0.25 with the exchange
-// through LDS; a launch of at most 16 steps costs the strips 0.55 us per step
-// on such rows.
+// through LDS; launches of 16 steps cost the strips 0.37 us per step on such
+// rows.
 constexpr int kRowMax = 1024;  // nodes, one workgroup's threads
 
 struct RowArgs {

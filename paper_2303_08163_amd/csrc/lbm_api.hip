@@ -1107,7 +1107,7 @@ int lbm_energy_history(lbm_handle *h, int64_t steps, int64_t every, const double
         set_error("a z-slab's steps need halo exchanges between them");
         return LBM_EINVAL;
     }
-    if (h->d.L.row && steps > 0 && every <= kRowSteps)
+    if (h->d.L.row && steps > 0 && row1_history(h->d.cfg.nx, every))
         return row_history(h, steps, every, U, rho_ref, out);
     int rc = lbm_energy(h, U, rho_ref, out);  // also checks U and rho_ref
     for (int64_t k = 1; rc == LBM_OK && k <= steps / every; ++k) {

@@ -92,6 +92,7 @@ struct RowEnergy {
     double rho_ref, U;
 };
 int row1_plan(int64_t nx);
+bool row1_history(int64_t nx, int64_t every);  // of a row that row1_plan takes
 int launch_row1(const Layout &L, const StepArgs &args, int dtype, bool corr, int steps, const RowEnergy *e,
                 hipStream_t s);
 int launch_strip2(const Layout &L, const StepArgs &args, int dtype, bool corr, int K, bool back, hipStream_t s);

@@ -265,11 +265,17 @@ static void (*row1_eq(int eq, bool one, bool energy))(RowArgs) {
 // One compute unit against the strips' whole chip: a row up to one wavefront per
 // SIMD is bound by the latency of a step either way and spares the launches,
 // beyond two the unit's arithmetic is slower.  us per step of a long run with
-// the correction, strips and row: FP64 64 nodes 0.56 and 0.19, 256 0.53 and 0.25, 512
-// 0.55 and 0.37, 768 0.55 and 0.48, 1024 0.55 and 0.60; ten steps at 768 nodes
-// take 5.3 and 6.9 us.  A history also spares the energy's launch: 10 steps and
-// a reading at 64 nodes 8.0 and 2.6 us, at 1024 8.4 and 6.7 (FP32 8.6 and 7.2).
+// the correction, strips and row: FP64 64 nodes 0.37 and 0.19, 256 0.38 and 0.25, 512
+// 0.40 and 0.37, 768 0.40 and 0.48, 1024 0.40 and 0.60.
 int row1_plan(int64_t nx) { return nx <= 512 ? 1 : nx <= kRowMax ? 2 : 0; }
+
+// A history also spares the energy's launch, which longer rows pay back for a few
+// steps between readings (us per reading, strips and row: FP64 512 nodes every 100
+// steps 44.5 and 38.6; 768 every 20 12.6 and 10.4, every 32 15.9 and 16.4; 1024 every 10
+// 8.0 and 6.6, every 16 9.5 and 10.3).
+bool row1_history(int64_t nx, int64_t every) {
+    return every <= kRowSteps && (row1_plan(nx) == 1 || (row1_plan(nx) == 2 && every * nx <= 15 * 1024));
+}
 
 int launch_row1(const Layout &L, const StepArgs &s, int dtype, bool corr, int steps, const RowEnergy *e,
                 hipStream_t stream) {
