@@ -130,7 +130,7 @@ typedef struct lbm_tuning {
                                  0 = default: the library's choice.  With block_x, block_y,
                                  nodes_per_thread, flags and layout left at their defaults
                                  and FP64 or FP32_DEV storage, launches take as many steps
-                                 as pay: D1Q3 8 or 16 (any number on rows of up to 512
+                                 as pay: D1Q3 8 to 32 (any number on rows of up to 256
                                  nodes), D2Q9 4 to 6, D3Q27 2 where sweeps or blocks pay; the
                                  results are bitwise those of 1 */
     int32_t time_rows;        /* time_block = 2: rows swept per workgroup (>= 1; 0 = default);

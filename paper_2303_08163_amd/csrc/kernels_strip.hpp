@@ -439,7 +439,7 @@ __global__ __launch_bounds__(kStripThreads) void k_strip1(StripArgs a) {
 //
 // Bound: the dependence chain of one collision (one wavefront per SIMD up to
 // 256 nodes), 0.19 us per step within one wavefront, 0.25 with the exchange
-// through LDS; launches of 16 steps cost the strips 0.37 us per step on such
+// through LDS; launches of 32 steps cost the strips 0.33 us per step on such
 // rows.
 constexpr int kRowMax = 1024;  // nodes, one workgroup's threads
 

@@ -220,8 +220,13 @@ int strip1_cols(int64_t nx, int dtype, int K) {
 
 // Most steps per launch of a run: long rows 8 (with more the halo's share grows
 // and the arithmetic is what bounds them), short rows, bound by the launch and
-// the latency of a step, 16.
-int strip1_steps(int64_t nx) { return strip1_wide(nx) ? 8 : 16; }
+// the latency of a step, 16 to 32: as long as a SIMD holds at most two of the
+// wavefronts of 64 own columns, 32 (us per step FP64, 16 / 24 / 32 / 40 steps: 3000 nodes
+// 0.34 / 0.29 / 0.27 / 0.27, 100,000 0.48 / 0.44 / 0.42 / 0.58, 200,000 0.65 / 0.61 / 0.75,
+// 400,000 1.00 / 0.93 / 1.19, 2^20 1.95 / 2.18 / 2.56; FP32 alike).
+int strip1_steps(int64_t nx) {
+    return strip1_wide(nx) ? 8 : nx > 400000 ? 16 : nx > 2 * 1024 * 64 ? 24 : 32;
+}
 
 int launch_strip1(const Layout &L, const StepArgs &s, int dtype, bool corr, int K, hipStream_t stream) {
     StripArgs a{};
@@ -265,16 +270,17 @@ static void (*row1_eq(int eq, bool one, bool energy))(RowArgs) {
 // One compute unit against the strips' whole chip: a row up to one wavefront per
 // SIMD is bound by the latency of a step either way and spares the launches,
 // beyond two the unit's arithmetic is slower.  us per step of a long run with
-// the correction, strips and row: FP64 64 nodes 0.37 and 0.19, 256 0.38 and 0.25, 512
-// 0.40 and 0.37, 768 0.40 and 0.48, 1024 0.40 and 0.60.
-int row1_plan(int64_t nx) { return nx <= 512 ? 1 : nx <= kRowMax ? 2 : 0; }
+// the correction, strips and row: FP64 64 nodes 0.33 and 0.19, 256 0.33 and 0.25, 512
+// 0.34 and 0.37, 1024 0.34 and 0.60.
+int row1_plan(int64_t nx) { return nx <= 256 ? 1 : nx <= kRowMax ? 2 : 0; }
 
 // A history also spares the energy's launch, which longer rows pay back for a few
-// steps between readings (us per reading, strips and row: FP64 512 nodes every 100
-// steps 44.5 and 38.6; 768 every 20 12.6 and 10.4, every 32 15.9 and 16.4; 1024 every 10
-// 8.0 and 6.6, every 16 9.5 and 10.3).
+// steps between readings (us per reading, strips and row: FP64 512 nodes every 32
+// steps 14.1 and 12.6, every 64 24.8 and 24.8; 768 every 20 10.9 and 10.4, every 24 12.0
+// and 12.4; 1024 every 10 8.3 and 6.6, every 16 9.9 and 10.3).
 bool row1_history(int64_t nx, int64_t every) {
-    return every <= kRowSteps && (row1_plan(nx) == 1 || (row1_plan(nx) == 2 && every * nx <= 15 * 1024));
+    return every <= kRowSteps &&
+           (row1_plan(nx) == 1 || (row1_plan(nx) == 2 && (nx <= 512 ? every <= 64 : every * nx <= 15 * 1024)));
 }
 
 int launch_row1(const Layout &L, const StepArgs &s, int dtype, bool corr, int steps, const RowEnergy *e,

@@ -15,8 +15,8 @@ def _lbm():
 
 
 # one wavefront, its edges, one and several wavefronts per SIMD, the longest
-# row of plain runs (512) and of histories (1024), and one beyond each
-SIZES = [1, 2, 3, 15, 63, 64, 65, 128, 255, 257, 511, 512, 513, 1000, 1024, 1025]
+# row of plain runs (256) and of histories (1024), and one beyond each
+SIZES = [1, 2, 3, 15, 63, 64, 65, 128, 255, 256, 257, 512, 513, 1000, 1024, 1025]
 
 
 @pytest.mark.parametrize("k", range(len(SIZES)))

@@ -109,6 +109,12 @@ D1_CASES = [  # nx, dtype, correction, equilibrium, step chunks
     ((1 << 22) + 3, "fp32_dev", False, "poly2", (11,)),
     ((1 << 23) + 2, "fp64", False, "product", (8, 1)),
     ((1 << 24) + 9, "fp32_dev", False, "entropic", (17,)),
+    # 32, 24 and 16 steps per launch, and one node beyond each
+    (600, "fp64", True, "entropic", (31, 32, 33, 100)),
+    (1 << 17, "fp32_dev", False, "entropic", (32, 3)),
+    ((1 << 17) + 1, "fp64", True, "product", (24, 25)),
+    (400000, "fp32_dev", True, "poly2", (50,)),
+    (400001, "fp64", False, "entropic", (33,)),
 ]
 
 
