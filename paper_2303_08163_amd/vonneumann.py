@@ -88,6 +88,7 @@ class RadiusEvaluator:
         # lockstep overlap on the GPU, one kernel's last wavefronts beside the
         # next one's first
         self.stream = torch.cuda.Stream(device=self.device)
+        self.stream.wait_stream(torch.cuda.current_stream(self.device))  # (the zeros above)
         for t in (self.states, self.out, self.scratch):
             t.record_stream(self.stream)  # not reused before that stream's work is done
         self.matrices = 0
