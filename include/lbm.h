@@ -200,8 +200,12 @@ int lbm_create_tuned(const lbm_config *cfg, const lbm_tuning *tuning, void *work
  * without synchronising.  Where launches are short (one step each, and D3Q27),
  * runs of 64 steps or more replay a captured HIP graph of 32 steps (the same
  * kernels and arguments, so bitwise the same results) to relieve the host's launch
- * rate; the graphs are captured by lbm_create.  nsteps = 0 is a no-op.  Errors: LBM_EINVAL (h NULL, nsteps < 0, nsteps > 1 on a z-slab,
- * which needs a halo exchange between steps); LBM_EDEVICE (launch failure). */
+ * rate; the graphs are captured by lbm_create.  nsteps = 0 is a no-op.  A call
+ * recorded into the caller's own graph advances the state at every replay if
+ * nsteps / time_block + nsteps % time_block (lbm_get_launch_info) is even; otherwise
+ * replays start from the same state again.  Errors: LBM_EINVAL (h NULL, nsteps < 0,
+ * nsteps > 1 on a z-slab, which needs a halo exchange between steps); LBM_EDEVICE
+ * (launch failure). */
 int lbm_step(lbm_handle *h, int64_t nsteps);
 
 /* Halo exchange of a z-slab (lbm_config.z_halo = 1).  A periodic domain split

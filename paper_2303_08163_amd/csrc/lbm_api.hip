@@ -866,13 +866,34 @@ static int enqueue_steps(lbm_handle *h, int cur, int K, hipStream_t s) {
     return enqueue_deep(h, cur, K, s);
 }
 
-// Launches of a graph of kGraphSteps steps (an odd number would leave the state in
-// the other buffer).
-static int graph_launches(const Layout &L) {
-    int launches = 0;
-    for (int64_t n = kGraphSteps; n > 0; n -= next_steps(L, n))
+// Launches that a run of n steps takes, and those it takes in launches of
+// time_block steps and single ones alone.
+static int64_t run_launches(const Layout &L, int64_t n) {
+    int64_t launches = 0;
+    for (; n > 0; n -= next_steps(L, n))
         ++launches;
     return launches;
+}
+static int64_t plain_launches(const Layout &L, int64_t n) { return n / L.tblock + n % L.tblock; }
+
+// Steps at the start of a run recorded into the caller's graph that go in launches
+// of time_block steps and single ones.  A replay finds the state where the run
+// found it only after an even number of launches; which step counts have one is
+// time_block's affair, not that of the longer launches: the fewest steps that bring
+// the run's number to the parity of time_block's.
+static int64_t captured_prefix(const Layout &L, int64_t n) {
+    int64_t m = 0;
+    while (m < n && (plain_launches(L, m) + run_launches(L, n - m) - plain_launches(L, n)) % 2 != 0)
+        ++m;
+    return m;
+}
+static bool is_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
 }
 
 // The graph of kGraphSteps steps starting from buffer `cur` (captured when the
@@ -884,7 +905,7 @@ static bool step_graph(lbm_handle *h, int cur) {
         return false;
     if (h->exec[cur])
         return true;
-    if (graph_launches(h->d.L) % 2 != 0) {
+    if (run_launches(h->d.L, kGraphSteps) % 2 != 0) {  // (the state would end in the other buffer)
         h->graphs_off = true;
         return false;
     }
@@ -958,8 +979,9 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
             d.steps += kGraphSteps;  // an even count of swaps: d.cur is unchanged
         }
     }
+    const int64_t plain = s + (d.L.deep && is_capturing(h->stream) ? captured_prefix(d.L, nsteps - s) : 0);
     while (s < nsteps) {
-        const int K = next_steps(d.L, nsteps - s);
+        const int K = s < plain ? (plain - s >= d.L.tblock ? d.L.tblock : 1) : next_steps(d.L, nsteps - s);
         int rc = enqueue_steps(h, d.cur, K, h->stream);
         if (rc != LBM_OK)
             return rc;
@@ -1080,6 +1102,10 @@ int lbm_energy(lbm_handle *h, const double *U, double rho_ref, double *out) {
 
 // A short row's history: steps and readings in one launch, or in as many as
 // kRowSteps steps each make.
+static int64_t row_launches(int64_t steps, int64_t every) {
+    const int64_t most = kRowSteps / every * every;
+    return (steps + most - 1) / most;
+}
 static int row_history(lbm_handle *h, int64_t steps, int64_t every, const double *U, double rho_ref, double *out) {
     int rc = check_reference(h, U, rho_ref);
     DomainState &d = h->d;
@@ -1107,7 +1133,10 @@ int lbm_energy_history(lbm_handle *h, int64_t steps, int64_t every, const double
         set_error("a z-slab's steps need halo exchanges between them");
         return LBM_EINVAL;
     }
-    if (h->d.L.row && steps > 0 && row1_history(h->d.cfg.nx, every))
+    // (not into a caller's graph that would find the state elsewhere at a replay, see captured_prefix)
+    if (h->d.L.row && steps > 0 && row1_history(h->d.cfg.nx, every) &&
+        !(is_capturing(h->stream) &&
+          (row_launches(steps, every) - steps / every * plain_launches(h->d.L, every)) % 2 != 0))
         return row_history(h, steps, every, U, rho_ref, out);
     int rc = lbm_energy(h, U, rho_ref, out);  // also checks U and rho_ref
     for (int64_t k = 1; rc == LBM_OK && k <= steps / every; ++k) {
