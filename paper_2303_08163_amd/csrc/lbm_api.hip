@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "kernels.hpp"
@@ -681,6 +682,46 @@ struct lbm_handle {
     double *host = nullptr;                    // pinned: results of lbm_moments (NULL: none could be had)
 };
 
+// Pinned blocks for the results of lbm_moments, one to a handle.  Freeing pinned
+// memory waits for all work on the device (59 ms behind another domain's queue, where
+// lbm_destroy otherwise takes 0.02 ms), so a block that a handle gives back serves
+// a later handle: slabs of kSlab blocks, kept until the process ends, no more
+// than handles were ever alive at once and kMost blocks (256 KiB) at most.
+// Handles beyond those have none and copy their results.
+namespace {
+class HostBlocks {
+    static constexpr int kSlab = 64, kMost = 1024;
+    std::mutex lock;
+    char *spare[kMost];
+    int spares = 0, made = 0;
+
+public:
+    double *take() {
+        std::lock_guard<std::mutex> g(lock);
+        if (spares == 0 && made < kMost) {
+            void *slab = nullptr;
+            if (hipHostMalloc(&slab, kSlab * kHostBytes, hipHostMallocPortable) != hipSuccess) {
+                (void)hipGetLastError();
+                return nullptr;
+            }
+            for (int k = 0; k < kSlab; ++k)
+                spare[spares++] = static_cast<char *>(slab) + k * kHostBytes;
+            made += kSlab;
+        }
+        return spares ? reinterpret_cast<double *>(spare[--spares]) : nullptr;
+    }
+    void give(double *block) {
+        std::lock_guard<std::mutex> g(lock);
+        spare[spares++] = reinterpret_cast<char *>(block);
+    }
+};
+// (never destroyed: handles may be closed while the process ends)
+HostBlocks &host_blocks() {
+    static HostBlocks *blocks = new HostBlocks();
+    return *blocks;
+}
+}  // namespace
+
 // Pack: plane 0's populations with c_z = -1 into `lower`, plane nz - 1's with
 // c_z = +1 into `upper`.  Unpack: `lower` into the halo plane below plane 0
 // (populations c_z = +1), `upper` into the halo plane above plane nz - 1
@@ -792,10 +833,7 @@ int lbm_create_tuned(const lbm_config *cfg, const lbm_tuning *tuning, void *work
         set_error("initial state has a node with rho <= 0 or |u_alpha| >= 1");
         return LBM_EDOMAIN;
     }
-    if (hipHostMalloc(reinterpret_cast<void **>(&h->host), kHostBytes, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        h->host = nullptr;
-    }
+    h->host = host_blocks().take();
     // capture the step graphs now, so that no later call pays for it
     h->graphs_off = L.deep != 0 && L.dim < 3;
     if (!L.zhalo) {
@@ -1269,6 +1307,7 @@ int lbm_destroy(lbm_handle *h) {
     if (!h)
         return LBM_OK;
     hipError_t e = hipStreamSynchronize(h->stream);
+    const bool synced = e == hipSuccess;
     // release everything even after a failure; report the first one
     auto keep = [&e](hipError_t r) {
         if (e == hipSuccess)
@@ -1282,8 +1321,9 @@ int lbm_destroy(lbm_handle *h) {
     }
     if (h->capture)
         keep(hipStreamDestroy(h->capture));
-    if (h->host)
-        keep(hipHostFree(h->host));
+    // (a block that a failed stream may still write to is not used again)
+    if (h->host && synced)
+        host_blocks().give(h->host);
     delete h;
     if (e != hipSuccess)
         return hip_fail(e, "destroy synchronise");
