@@ -26,17 +26,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# steps per launch of the library's default runs on the grids timed here: D3Q27 256^3
-# (two-step sweeps), D2Q9 4096^2 (strips); lbm_get_launch_info describes the one-step
-# kernel that ends a run
-D2Q9_STEPS = {"fp32_dev": 4, "fp64": 6}
-
-
-def d3q27_steps(n: int) -> int:
-    """Sweeps and blocks take two; cubes between them one."""
-    return 2 if 2 * 27 * 4 * n ** 3 > 96 << 20 or n <= 48 else 1
-
-
 METRIC = "MLUPS & % HBM roofline (D3Q27 256³ FP32); batched solves/s, p99 latency"
 PROFILE_SUMMARY = os.path.join(ROOT, "profiles", "sweep3_d3q27_fp32dev_256.md")
 
@@ -447,13 +436,14 @@ def bench_variants(steps: int = 100, warmup: int = 10) -> dict:
     for eq in ("entropic", "poly2", "product"):
         for corr in (False, True):
             dom = lbm.Domain(rd, ud, 0.5005, dtype="fp32_dev", bulk_correction=corr, equilibrium=eq, stream=stream)
-            out[f"d3q27_256_fp32_{eq}{'_corrected' if corr else ''}"] = timed(dom, 256 ** 3, 216 / d3q27_steps(256))
+            rec = timed(dom, 256 ** 3, 216 / dom.run_info()["steps"])
+            out[f"d3q27_256_fp32_{eq}{'_corrected' if corr else ''}"] = rec
             dom.close()
     # full FP64 storage of the headline workload (432 B per node and launch)
     for corr in (False, True):
         dom = lbm.Domain(rd, ud, 0.5005, dtype="fp64", bulk_correction=corr, stream=stream)
-        rec = timed(dom, 256 ** 3, 432 / d3q27_steps(256))
-        rec["kernel"] = dom.launch_info()
+        rec = timed(dom, 256 ** 3, 432 / dom.run_info()["steps"])
+        rec["kernel"] = dom.run_info()
         out[f"d3q27_256_fp64_entropic{'_corrected' if corr else ''}"] = rec
         dom.close()
     del rd, ud
@@ -526,7 +516,7 @@ def bench_d1q3(steps: int = 200, warmup: int = 64) -> dict:
     out = {}
 
     def timed(dom, nodes, bytes_per_lup):
-        k = dom.launch_info()["time_block"]
+        k = dom.run_info()["steps"]
         dom.step(warmup)
         torch.cuda.synchronize()
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -585,7 +575,7 @@ def bench_d2q9(steps: int = 100, warmup: int = 200) -> dict:
             for name, tun in (("default", None), ("two_steps_per_launch", lbm.make_tuning(time_block=2)),
                               ("one_step_per_launch", lbm.make_tuning(time_block=1))):
                 dom = lbm.Domain(r2, u2, 0.5001, dtype=dt, bulk_correction=corr, stream=stream, tuning=tun)
-                info = dom.launch_info()
+                info = dom.run_info()
                 dom.step(warmup)
                 torch.cuda.synchronize()
                 reps = []
@@ -600,13 +590,13 @@ def bench_d2q9(steps: int = 100, warmup: int = 200) -> dict:
                 dom.close()
                 sec = min(reps)
                 mlups = 4096 ** 2 / sec / 1e6
-                k = info["time_block"] if tun else D2Q9_STEPS[dt]
+                k = info["steps"]
                 own = 2 * 9 * s * 4096 ** 2 / (k * sec) / 1e9  # bytes of one launch / its time
                 key = f"{dt}_{name}{'_corrected' if corr else ''}"
                 out[key] = {
                     "mlups": round(mlups, 1), "us_per_step": round(sec * 1e6, 1),
                     "us_per_step_reps": [round(v * 1e6, 1) for v in reps], "steps_per_launch": k,
-                    "kernel": info["kernel"] if tun else "k_strip2", "gbs": round(own, 1), "frac": round(own / HBM_PEAK_GBS, 4),
+                    "kernel": info["kernel"], "gbs": round(own, 1), "frac": round(own / HBM_PEAK_GBS, 4),
                     "gbs_2Qs_per_update": round(mlups * 1e6 * 2 * 9 * s / 1e9, 1), "domain_error": d["domain_error"]}
                 if k == 2:
                     out[key]["roofline_valu"] = valu_roofline(f"d2q9_4096.{key}", k * sec)
@@ -778,7 +768,7 @@ def main() -> int:
     rho0, u0 = workloads.taylor_green_3d(n, u0=0.05)
     stream = torch.cuda.current_stream(dev)
     dom = lbm.Domain(rho0, u0, tau, dtype="fp32_dev", bulk_correction=False, stream=stream)
-    launch = dom.launch_info()
+    launch, run = dom.launch_info(), dom.run_info()
     del rho0, u0
     nodes = n ** 3
     dom.step(args.warmup)
@@ -807,7 +797,7 @@ def main() -> int:
     sec = ms / 1e3
     mlups = nodes * args.steps / sec / 1e6
     bytes_per_launch = 2 * 27 * 4  # per node
-    per_launch_s = d3q27_steps(n) * sec / args.steps
+    per_launch_s = run["steps"] * sec / args.steps
     achieved = bytes_per_launch * nodes / per_launch_s / 1e9
     traffic = measured_traffic()
 
@@ -838,10 +828,11 @@ def main() -> int:
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "kernel": "k_sweep3<D3Q27, FP32 deviations/FP64 arithmetic, no correction>, two steps per launch",
-            "bytes_per_node_update": bytes_per_launch / d3q27_steps(n), "steps_per_launch": d3q27_steps(n),
+            "kernel": f"{run['kernel']} (D3Q27, FP32 deviations/FP64 arithmetic, no correction)",
+            "bytes_per_node_update": bytes_per_launch / run["steps"], "steps_per_launch": run["steps"],
             "launch_avg_ms": round(per_launch_s * 1e3, 5),
         },
+        "run": run,
         "launch": launch,
         "wall_s_timed_region": round(t_wall, 4),
         "repetitions_ms_per_step": [round(v, 5) for v in reps],

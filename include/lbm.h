@@ -311,6 +311,28 @@ typedef struct lbm_launch_info {
  * out NULL). */
 int lbm_get_launch_info(const lbm_handle *h, lbm_launch_info *out);
 
+/* The launch that a domain's runs are made of: the longest one of its
+ * configuration and tuning (a run's last launches may take fewer steps, down to
+ * the one-step kernel of lbm_get_launch_info).  Without launches longer than
+ * time_block it is lbm_get_launch_info's. */
+enum {
+    LBM_KERNEL_STRIP = 5, /* D1Q3 and D2Q9: strips of columns, the intermediate states in registers */
+    LBM_KERNEL_BLOCK = 6, /* D2Q9 and D3Q27: blocks of a small domain, every row at once */
+    LBM_KERNEL_SWEEP = 7, /* D3Q27: column blocks swept plane by plane */
+    LBM_KERNEL_ROW = 8    /* D1Q3: the whole row in one workgroup */
+};
+typedef struct lbm_run_info {
+    int32_t kernel;             /* LBM_KERNEL_* */
+    int32_t steps;              /* steps of the launch */
+    int32_t cols, rows, planes; /* nodes that a workgroup (a strip: a wavefront) owns, per axis */
+    int32_t reserved[3];
+} lbm_run_info;
+
+/* Fill *out for a configuration and tuning (NULL: default), as lbm_create_tuned
+ * would choose (host-only; no GPU call, no handle).  Errors: LBM_EINVAL (cfg or out
+ * NULL, or what lbm_create_tuned refuses). */
+int lbm_get_run_info(const lbm_config *cfg, const lbm_tuning *tuning, lbm_run_info *out);
+
 /* Checkpoint and restart: the current state as the library stores it (its
  * private format: the storage type, layout and padding of the handle's
  * configuration and tuning), so that a restart is bit-exact for every storage

@@ -1272,6 +1272,12 @@ int lbm_ceiling_copy(const void *src, void *dst, size_t bytes, void *stream) {
     return LBM_OK;
 }
 
+// Kernel of a launch of time_block steps.
+static int block_kernel(const Layout &L) {
+    return L.tblock > 1 ? (L.dim == 1 ? LBM_KERNEL_MULTI_STEP : LBM_KERNEL_TWO_STEP)
+                        : (L.npt > 1 ? LBM_KERNEL_VECTOR : LBM_KERNEL_NODE);
+}
+
 int lbm_get_launch_info(const lbm_handle *h, lbm_launch_info *out) {
     if (!h || !out) {
         set_error("NULL handle or output");
@@ -1279,8 +1285,7 @@ int lbm_get_launch_info(const lbm_handle *h, lbm_launch_info *out) {
     }
     const Layout &L = h->d.L;
     lbm_launch_info r{};
-    r.kernel = L.tblock > 1 ? (L.dim == 1 ? LBM_KERNEL_MULTI_STEP : LBM_KERNEL_TWO_STEP)
-                            : (L.npt > 1 ? LBM_KERNEL_VECTOR : LBM_KERNEL_NODE);
+    r.kernel = block_kernel(L);
     r.nodes_per_thread = L.npt;
     r.row_wave = L.rowwave ? 1 : 0;
     r.flags = L.flags;
@@ -1291,6 +1296,48 @@ int lbm_get_launch_info(const lbm_handle *h, lbm_launch_info *out) {
     r.time_cols = L.tblock > 1 ? L.t2_tx : 0;
     r.time_rows = L.tblock == 2 && L.dim == 2 ? L.t2_rows : 0;
     r.graph_steps = (h->exec[0] || h->exec[1]) && !h->graphs_off ? kGraphSteps : 0;
+    *out = r;
+    return LBM_OK;
+}
+
+int lbm_get_run_info(const lbm_config *cfg, const lbm_tuning *tuning, lbm_run_info *out) {
+    if (!cfg || !out) {
+        set_error("NULL configuration or output");
+        return LBM_EINVAL;
+    }
+    Layout L;
+    const int rc = validate_config(cfg, tuning, &L);
+    if (rc != LBM_OK)
+        return rc;
+    lbm_run_info r{};
+    r.rows = r.planes = 1;
+    if (L.deep && L.dim == 1) {
+        r.kernel = L.row == 1 ? LBM_KERNEL_ROW : LBM_KERNEL_STRIP;
+        r.cols = L.row == 1 ? (int)cfg->nx : strip1_cols(cfg->nx, cfg->dtype, L.deep);
+    } else if (L.block2.rpt) {
+        r.kernel = LBM_KERNEL_BLOCK;
+        r.cols = L.block2.own_x;
+        r.rows = L.block2.own_y;
+    } else if (L.deep && L.dim == 2) {
+        r.kernel = LBM_KERNEL_STRIP;
+        r.cols = 64 - 2 * (L.deep - 1);
+        r.rows = L.strip_rows[L.deep == 6];
+    } else if (L.block3.own_x) {
+        r.kernel = LBM_KERNEL_BLOCK;
+        r.cols = L.block3.own_x;
+        r.rows = L.block3.own_y;
+        r.planes = L.block3.own_z;
+    } else if (L.deep) {
+        r.kernel = LBM_KERNEL_SWEEP;
+        r.cols = L.sweep3.w - 2;
+        r.rows = L.sweep3.rows;
+        r.planes = L.sweep3.planes;
+    } else {
+        r.kernel = block_kernel(L);
+        r.cols = L.tblock > 1 ? L.t2_tx : L.block_x * L.npt;
+        r.rows = L.tblock == 1 ? L.block_y : std::max(1, L.t2_rows);
+    }
+    r.steps = L.deep ? L.deep : L.tblock;
     *out = r;
     return LBM_OK;
 }

@@ -29,7 +29,8 @@ LBM_EQ_ENTROPIC, LBM_EQ_POLY2, LBM_EQ_PRODUCT = 0, 1, 2
 EQUILIBRIA = {"entropic": LBM_EQ_ENTROPIC, "poly2": LBM_EQ_POLY2, "product": LBM_EQ_PRODUCT}
 
 LBM_KERNEL_NODE, LBM_KERNEL_VECTOR, LBM_KERNEL_TWO_STEP, LBM_KERNEL_MULTI_STEP = 1, 2, 3, 4
-KERNEL_NAMES = {1: "node", 2: "vector", 3: "two_step", 4: "multi_step"}
+LBM_KERNEL_STRIP, LBM_KERNEL_BLOCK, LBM_KERNEL_SWEEP, LBM_KERNEL_ROW = 5, 6, 7, 8
+KERNEL_NAMES = {1: "node", 2: "vector", 3: "two_step", 4: "multi_step", 5: "strip", 6: "block", 7: "sweep", 8: "row"}
 
 DTYPES = {"fp64": LBM_FP64, "fp32_dev": LBM_FP32_DEV, "fp32_dev_mixed": LBM_FP32_DEV_MIXED,
           "fp32_dev_f32": LBM_FP32_DEV_F32}
@@ -68,6 +69,16 @@ class lbm_launch_info(ctypes.Structure):
                 ("flags", ctypes.c_int32), ("block_x", ctypes.c_int32), ("block_y", ctypes.c_int32),
                 ("layout", ctypes.c_int32), ("time_block", ctypes.c_int32), ("time_cols", ctypes.c_int32),
                 ("time_rows", ctypes.c_int32), ("graph_steps", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+    def as_dict(self) -> dict:
+        d = {k: getattr(self, k) for k, _ in self._fields_ if k != "reserved"}
+        d["kernel"] = KERNEL_NAMES.get(d["kernel"], d["kernel"])
+        return d
+
+
+class lbm_run_info(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("steps", ctypes.c_int32), ("cols", ctypes.c_int32),
+                ("rows", ctypes.c_int32), ("planes", ctypes.c_int32), ("reserved", ctypes.c_int32 * 3)]
 
     def as_dict(self) -> dict:
         d = {k: getattr(self, k) for k, _ in self._fields_ if k != "reserved"}
@@ -121,7 +132,7 @@ EXPORTS = ("lbm_workspace_bytes", "lbm_workspace_bytes_tuned", "lbm_create", "lb
            "lbm_vn_spectra", "lbm_vn_max_radius", "lbm_halo_bytes", "lbm_halo_pack", "lbm_halo_unpack",
            "lbm_step_halo", "lbm_state_bytes", "lbm_save_state", "lbm_load_state", "lbm_get_launch_info",
            "lbm_pool_admit_async", "lbm_pool_collect", "lbm_ceiling_stream", "lbm_ceiling_copy",
-           "lbm_vn_max_radius_noalloc")
+           "lbm_vn_max_radius_noalloc", "lbm_get_run_info")
 
 
 def load_library(path: str = LIB_PATH):
@@ -151,6 +162,7 @@ def load_library(path: str = LIB_PATH):
         "lbm_moments": (ctypes.c_int, [vp, vp, vp, ctypes.POINTER(lbm_diag)]),
         "lbm_get_populations": (ctypes.c_int, [vp, vp]),
         "lbm_get_launch_info": (ctypes.c_int, [vp, ctypes.POINTER(lbm_launch_info)]),
+        "lbm_get_run_info": (ctypes.c_int, [cfgp, ctypes.POINTER(lbm_tuning), ctypes.POINTER(lbm_run_info)]),
         "lbm_ceiling_stream": (ctypes.c_int, [vp, i64]),
         "lbm_ceiling_copy": (ctypes.c_int, [vp, vp, sz, vp]),
         "lbm_energy": (ctypes.c_int, [vp, ctypes.POINTER(ctypes.c_double), ctypes.c_double, vp]),
@@ -271,6 +283,13 @@ def lbm_get_populations(h, out: int) -> None:
 def lbm_get_launch_info(h) -> dict:
     info = lbm_launch_info()
     _check(load_library().lbm_get_launch_info(h, ctypes.byref(info)), "lbm_get_launch_info")
+    return info.as_dict()
+
+
+def lbm_get_run_info(cfg: lbm_config, tuning: lbm_tuning | None = None) -> dict:
+    info = lbm_run_info()
+    tun = ctypes.byref(tuning) if tuning is not None else None
+    _check(load_library().lbm_get_run_info(ctypes.byref(cfg), tun, ctypes.byref(info)), "lbm_get_run_info")
     return info.as_dict()
 
 
@@ -529,6 +548,11 @@ class Domain:
         """The launch the library chose for this domain (kernel kind, nodes per
         thread, row-wave form, cache hints, workgroup shape, steps per launch)."""
         return lbm_get_launch_info(self.handle)
+
+    def run_info(self) -> dict:
+        """The launch that this domain's runs are made of: kernel, steps, and the
+        nodes per axis that a workgroup (a strip: a wavefront) owns."""
+        return lbm_get_run_info(self.cfg, self.tuning)
 
     def save_state(self):
         """Checkpoint: a CUDA uint8 tensor holding the stored state (bit-exact),
