@@ -88,6 +88,16 @@ static Block2Geom block2_geom(int64_t nx, int64_t ny, int K, double *us) {
     return g;
 }
 
+// One step per launch, us: the launch, and one read and one write of both
+// buffers (row padding included) at the rate measured within and beyond the
+// last-level cache (24 shapes from 1 x 3000 to 12 million nodes, within 25 % for rows of
+// 8 nodes and more; shorter rows run slower than this).
+static double one_step2_us(const Layout &L) {
+    const double bytes = 2.0 * (double)L.buf_bytes, launch = L.elem == 4 ? 2.65 : 2.8;
+    const double rate = bytes > (double)(256 << 20) ? 5.85e6 : L.elem == 4 ? 6.8e6 : 8.0e6;  // bytes per us
+    return launch + bytes / rate;
+}
+
 // Which form the runs of a D2Q9 domain take: strips of 4 steps per launch (FP32)
 // or 6 and 4 (FP64), blocks of 5 or 4, by the estimated time per step, or neither.
 // FP32 strips are bound by the FP64 arithmetic at 4 steps already (4096^2, us
@@ -95,27 +105,37 @@ static Block2Geom block2_geom(int64_t nx, int64_t ny, int K, double *us) {
 // SIMD less); FP64 by HBM until 6 (4 steps 131.8, 5 112.6, 6 96.6, 8 118.6 with
 // one wavefront per SIMD).  Blocks are best with 5 steps (us per step, FP64 3 / 4 / 5 /
 // 6 / 8 steps: 64^2 - / 1.25 / 1.13 / 1.23 / 1.22, 300^2 1.95 / 1.87 / 1.65 / 1.94 /
-// 1.83), FP32 with several per compute unit 4 (512^2 3.35, 5 steps 3.43).  They win below about 700^2 (us per step, FP64 blocks /
-// strips: 512^2 3.2 / 4.2, 700 x 600 3.9 / 5.1; 1024^2 with four steps 9.2 / 8.3).
+// 1.83), FP32 with several per compute unit 4 (512^2 3.35, 5 steps 3.43).  They win
+// below about 700^2 (us per step, FP64 blocks / strips: 512^2 3.2 / 4.2, 700 x 600 3.9 /
+// 5.1; 1024^2 with four steps 9.2 / 8.3).
+// Both spend 64 lanes a row and collide halo rows again, so narrow and flat domains
+// run sooner with time_block steps per launch (us per step, strip or block / one: FP32
+// 8 x 375,000 98 / 32, 16 x 187,500 50 / 31, 24 x 125,000 35 / 44, 16 x 18,750 7.9 / 5.5,
+// 24 x 12,500 5.6 / 6.3, 3,000,000 x 1 52 / 33, 600,000 x 5 26 / 33; FP64 4 x 750,000 162 /
+// 102, 12 x 250,000 57 / 85, 8 x 37,500 11.1 / 8.3, 16 x 18,750 6.8 / 8.0).  The FP64
+// estimates run low there, blocks by up to 1.5, strips by up to 1.25: hence `low`.
 void plan2(const lbm_config *cfg, Layout &L) {
     if (L.dim != 2 || L.layout != LBM_LAYOUT_ROWS || (cfg->dtype != LBM_FP64 && cfg->dtype != LBM_FP32_DEV))
         return;
     if (cfg->nx > (1 << 28))  // byte offsets inside a row are 32-bit
         return;
-    double us4, us6 = 0.0, usb;
     const bool six = cfg->dtype == LBM_FP64;
+    double us4, us6, usb;
     L.strip_rows[0] = strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 4, &us4);
-    L.strip_rows[1] = six ? strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 6, &us6) : 0;
+    if (six)
+        L.strip_rows[1] = strip2_rows(cfg->nx, cfg->ny, cfg->dtype, 6, &us6);
+    const double strips = six ? us6 / 6 : us4 / 4;
     int K = 5;
     Block2Geom g = block2_geom(cfg->nx, cfg->ny, K, &usb);
     if (!six && (int64_t)g.tiles_x * g.tiles_y > 256)
         g = block2_geom(cfg->nx, cfg->ny, K = 4, &usb);
-    if (L.tblock == 1 && usb / K < (six ? us6 / 6 : us4 / 4)) {
+    const bool blocks = L.tblock == 1 && usb / K < strips;
+    const double low = !six ? 1.0 : blocks ? 1.3 : 1.2;
+    if (low * (blocks ? usb / K : strips) >= one_step2_us(L))
+        return;
+    if (blocks)
         L.block2 = g;
-        L.deep = K;
-    } else {
-        L.deep = six ? 6 : 4;
-    }
+    L.deep = blocks ? K : six ? 6 : 4;
 }
 
 template <int DT, int K, int EQ, bool BACK>
