@@ -22,7 +22,7 @@ namespace lbm {
 // wins (256^3, us per step: FP32 64 x 8 x 128 planes, 256 workgroups, 433; 64 x 9 x
 // 128, 232, 485; 64 x 9 x 24, 1276, 457; FP64 64 x 4 x 256, 256, 742; 32 x 13 x 32,
 // 1280, 810; 32 x 13 x 256, 160, 1023).
-Sweep3Geom sweep3_geom(int64_t nx, int64_t ny, int64_t nz, size_t elem) {
+static Sweep3Geom sweep3_geom(int64_t nx, int64_t ny, int64_t nz, size_t elem, double *us) {
     Sweep3Geom best{};
     double best_cost = -1.0;
     const double T1 = elem == 4 ? 0.0102 : 0.0203;
@@ -54,7 +54,40 @@ Sweep3Geom sweep3_geom(int64_t nx, int64_t ny, int64_t nz, size_t elem) {
             }
         }
     }
+    *us = best_cost;
     return best;
+}
+
+// One step per launch, us.  Within the last-level cache: the launch, the stored
+// nodes (row padding included), and the wavefronts of a SIMD, lanes outside the
+// domain and vector lanes counted.  Beyond it, and for the vector kernel, whose
+// accesses pass the cache by: one read and one write at 5.3 bytes per ns.  (110
+// domains from 64 x 40 x 100 to 130 x 256^2: within 8 %, rows of 256 nodes and more
+// up to 1.3 times slower.)
+static double one_step3_us(const lbm_config *cfg, const Layout &L) {
+    const double bytes = 2.0 * (double)L.buf_bytes, stored = (double)L.buf_bytes / (27.0 * (double)L.elem);
+    if (L.npt > 1 || bytes > (double)(256 << 20))
+        return bytes / 5.3e6;
+    const int64_t tiles =
+        (cfg->nx + L.block_x - 1) / L.block_x * ((cfg->ny + L.block_y - 1) / L.block_y) * cfg->nz;
+    const double waves = std::ceil((double)(tiles * (L.block_x * L.block_y / 64)) / 1024.0);
+    return L.elem == 4 ? 2.85 + 0.0175e-3 * stored + 0.69 * waves : 3.11 + 0.040e-3 * stored + 0.80 * waves;
+}
+
+// Whether sweeps of this geometry (and estimate, us per launch) beat one step per launch.
+// The estimate holds for full tiles and many planes; the first two of a sweep's
+// planes + 2 iterations take no second step, and neither do the lanes outside the
+// domain: both taken into account, it is within 15 % of 136 domains of 16 x 128 x 128
+// to 150 x 256^2 nodes.  us per step, sweeps / one step: FP32 16 x 4 x 25,000 129 / 74,
+// 16 x 8 x 12,500 95 / 76, 16 x 256^2 43 / 34, 1000^2 x 1 45 / 32, 600^2 x 2 28 / 24,
+// 128 x 64^2 18.2 / 17.2, 33 x 128^2 22 / 27, 20 x 256^2 65 / 86; FP64 16 x 4 x 25,000
+// 140 / 129, 35 x 86 x 57 18.7 / 16.2, 16 x 256^2 70 / 88, 64^3 15.7 / 17.5.
+static bool sweep3_pays(const lbm_config *cfg, const Layout &L, const Sweep3Geom &g, double us) {
+    const int64_t own_x = (cfg->nx + g.w - 3) / (g.w - 2) * (g.w - 2),
+                  own_y = (cfg->ny + g.rows - 1) / g.rows * g.rows;
+    const double used = (double)cfg->nx / (double)own_x * ((double)cfg->ny / (double)own_y);
+    const double step = us / 2 * (g.planes + 0.7) / (g.planes + 2) * (0.5 + 0.5 * used);
+    return step < 0.965 * one_step3_us(cfg, L);
 }
 
 // Block of k_block3 with the least estimated time, and that time in us per
@@ -99,15 +132,18 @@ void plan3(const lbm_config *cfg, Layout &L) {
         (cfg->dtype != LBM_FP64 && cfg->dtype != LBM_FP32_DEV))
         return;
     // byte offsets inside a plane (a block: inside the buffer) are 32-bit
+    double us;
     if (2 * L.buf_bytes > kSweep3Bytes && cfg->nx >= 16 && cfg->ny >= 4 &&
         L.plane * (int64_t)L.elem < ((int64_t)1 << 31)) {
-        L.sweep3 = sweep3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem);
-        L.deep = 2;
+        const Sweep3Geom g = sweep3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem, &us);
+        if (sweep3_pays(cfg, L, g, us)) {
+            L.sweep3 = g;
+            L.deep = 2;
+        }
     } else if (L.n <= kBlock3Nodes) {
         // one step per launch took about (us) 3.2 + 0.034 n / 1000 with FP32 storage,
         // 4.0 + 0.056 n / 1000 with FP64 (16^3 3.7 / 4.2, 40^3 5.5 / 7.5, 56^3 9.2 / 14.5)
         const double one = L.elem == 4 ? 3.2 + 0.034e-3 * (double)L.n : 4.0 + 0.056e-3 * (double)L.n;
-        double us;
         const Block3Geom g = block3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem, &us);
         if (us > 0.0 && us / 2 < 0.86 * one) {  // (the estimate runs up to 15 % low)
             L.block3 = g;

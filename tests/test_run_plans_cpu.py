@@ -43,3 +43,33 @@ def _steps(shape, dtype):
 ])
 def test_d2q9(shape, dtype, several):
     assert (_steps(shape, dtype) > 2) == several
+
+
+# D3Q27 domains large enough for sweeps
+@pytest.mark.parametrize("shape,dtype,several", [
+    ((16, 4, 25000), "fp32_dev", False),    # 129 / 74
+    ((16, 8, 12500), "fp32_dev", False),    # 95 / 76
+    ((16, 256, 256), "fp32_dev", False),    # 43 / 34
+    ((1000, 1000, 1), "fp32_dev", False),   # 45 / 32
+    ((600, 600, 2), "fp32_dev", False),     # 28 / 24
+    ((1024, 512, 1), "fp32_dev", False),    # 26 / 22
+    ((128, 64, 64), "fp32_dev", False),     # 18.2 / 17.2
+    ((16, 4, 25000), "fp64", False),        # 140 / 129
+    ((35, 86, 57), "fp64", False),          # 18.7 / 16.2
+    ((16, 128, 128), "fp64", False),        # 18.0 / 17.5
+    ((16, 256, 256), "fp64", True),         # 70 / 88
+    ((16, 8, 12500), "fp64", True),         # 108 / 130
+    ((20, 256, 256), "fp32_dev", True),     # 65 / 86
+    ((33, 128, 128), "fp32_dev", True),     # 22 / 27
+    ((36, 200, 256), "fp64", True),
+    ((33, 200, 200), "fp32_dev", True),
+    ((512, 4, 512), "fp32_dev", True),      # 31 / 47
+    ((100, 7, 1000), "fp32_dev", True),     # 22 / 26
+    ((64, 64, 64), "fp64", True),           # 15.7 / 17.5
+    ((128, 128, 128), "fp32_dev", True),
+    ((256, 256, 256), "fp32_dev", True),
+    ((256, 256, 256), "fp64", True),
+    ((150, 131, 120), "fp64", True),
+])
+def test_d3q27_sweeps(shape, dtype, several):
+    assert (_steps(shape, dtype) == 2) == several
