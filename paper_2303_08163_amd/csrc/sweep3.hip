@@ -143,7 +143,15 @@ void plan3(const lbm_config *cfg, Layout &L) {
     } else if (L.n <= kBlock3Nodes) {
         // one step per launch took about (us) 3.2 + 0.034 n / 1000 with FP32 storage,
         // 4.0 + 0.056 n / 1000 with FP64 (16^3 3.7 / 4.2, 40^3 5.5 / 7.5, 56^3 9.2 / 14.5)
-        const double one = L.elem == 4 ? 3.2 + 0.034e-3 * (double)L.n : 4.0 + 0.056e-3 * (double)L.n;
+        double one = L.elem == 4 ? 3.2 + 0.034e-3 * (double)L.n : 4.0 + 0.056e-3 * (double)L.n;
+        // That is high for FP32 rows that fill their padding and their wavefronts: of 2700
+        // ragged domains of up to 200,000 nodes that took blocks by it, 69 ran up to 1.24
+        // times slower than with one step per launch (us per step, blocks / one:
+        // 147 x 5 x 40 4.6 / 3.7, 108 x 23 x 19 5.2 / 4.3, 111 x 20 x 22 5.0 / 4.3; 48^3 5.9 /
+        // 6.9).  By the lower of the two estimates 22 do, at most 1.12 times.  (The vector
+        // kernel is the slower one there: 256 x 16^2 4.9 / 7.3.)
+        if (L.elem == 4 && L.npt == 1)
+            one = std::min(one, one_step3_us(cfg, L));
         const Block3Geom g = block3_geom(cfg->nx, cfg->ny, cfg->nz, L.elem, &us);
         if (us > 0.0 && us / 2 < 0.86 * one) {  // (the estimate runs up to 15 % low)
             L.block3 = g;

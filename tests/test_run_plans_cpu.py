@@ -73,3 +73,23 @@ def test_d2q9(shape, dtype, several):
 ])
 def test_d3q27_sweeps(shape, dtype, several):
     assert (_steps(shape, dtype) == 2) == several
+
+
+# small D3Q27 domains
+@pytest.mark.parametrize("shape,dtype,several", [
+    ((147, 5, 40), "fp32_dev", False),    # 4.6 / 3.7
+    ((108, 23, 19), "fp32_dev", False),   # 5.2 / 4.3
+    ((108, 9, 49), "fp32_dev", False),    # 5.0 / 4.2
+    ((111, 20, 22), "fp32_dev", False),   # 5.0 / 4.3
+    ((115, 30, 15), "fp32_dev", False),   # 5.3 / 4.6
+    ((101, 31, 14), "fp32_dev", False),   # 5.2 / 4.4
+    ((16, 16, 16), "fp32_dev", True),     # 2.7 / 3.7
+    ((32, 32, 32), "fp32_dev", True),
+    ((40, 40, 40), "fp32_dev", True),
+    ((256, 16, 16), "fp32_dev", True),    # 4.9 / 7.3
+    ((48, 48, 48), "fp32_dev", True),     # 5.9 / 6.9
+    ((48, 48, 48), "fp64", True),         # 8.1 / 9.9
+    ((16, 16, 256), "fp64", True),
+])
+def test_d3q27_blocks(shape, dtype, several):
+    assert (_steps(shape, dtype) == 2) == several
