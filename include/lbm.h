@@ -361,7 +361,7 @@ int lbm_load_state(lbm_handle *h, const void *src, size_t bytes, int64_t steps);
  *   rho_ref  > 0 and finite.
  *   out      device pointer to one double, written when the stream reaches
  *            the call.
- * Enqueues one kernel and returns without synchronising, so that an energy
+ * Enqueues one or two kernels and returns without synchronising, so that an energy
  * history E(t) can be recorded step by step into a device array and read
  * once.  The sum is taken in a fixed order (bitwise reproducible).  Errors:
  * LBM_EINVAL (h or out NULL, rho_ref <= 0 or not finite, U not finite);

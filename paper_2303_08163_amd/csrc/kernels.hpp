@@ -703,7 +703,7 @@ struct EnergyArgs {
     double rho_ref;
     double U[3];
     double *partials;   // gridDim.x values
-    unsigned *arrived;  // as in MomentArgs
+    unsigned *arrived;  // as in MomentArgs; NULL: k_sum_partials folds
     double *out;
 };
 
@@ -755,6 +755,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_energy(EnergyArgs a) {
         acc += node_energy<DIM>(f, DEV ? a.rho0 : 0.0, a.rho_ref, half_cs2_over_rho, a.U);
     }
     double r = block_sum(acc);
+    if (!a.arrived) {
+        if (threadIdx.x == 0)
+            a.partials[blockIdx.x] = r;
+        return;
+    }
     if (!last_workgroup(a.arrived, [&] { put_partial(a.partials + blockIdx.x, r); }))
         return;
     acc = 0.0;
@@ -763,6 +768,17 @@ __global__ __launch_bounds__(kReduceThreads) void k_energy(EnergyArgs a) {
     r = block_sum(acc);
     if (threadIdx.x == 0)
         *a.out = r;
+}
+
+// The partials of a k_energy launch without a counter, by one workgroup.
+static __global__ __launch_bounds__(kReduceThreads) void k_sum_partials(const double *partials, int count,
+                                                                        double *out) {
+    double acc = 0.0;
+    for (int b = threadIdx.x; b < count; b += blockDim.x)
+        acc += partials[b];
+    const double r = block_sum(acc);
+    if (threadIdx.x == 0)
+        *out = r;
 }
 
 struct ExportArgs {

@@ -638,18 +638,30 @@ int domain_export(DomainState &d, hipStream_t s, double *out) {
     return LBM_OK;
 }
 
+// Up to 100,000 nodes one launch: its last workgroup folds the partials.  Beyond, up
+// to 1024 workgroups keep the loads busy, and their arrivals at the counter, one after
+// another, take longer than a second launch: us per energy, one launch of 256 to
+// 512 workgroups / two of 1024 and one: 300^2 6.2 / 6.4, 48^3 FP64 7.4 / 6.9, 512^2 7.4 /
+// 7.0, 800 x 700 FP32 10.4 / 6.9, 1024^2 FP32 13.6 / 9.1, FP64 17.7 / 14.7, 4096^2 FP32
+// 118 / 104.
+constexpr int64_t kEnergyOneLaunch = 100000;
 int domain_energy(DomainState &d, hipStream_t s, const double *U, double rho_ref, double *out) {
     const Layout &L = d.L;
-    const bool dev = d.cfg.dtype != LBM_FP64;
+    const bool dev = d.cfg.dtype != LBM_FP64, one = L.n <= kEnergyOneLaunch;
+    // (beyond kEnergyOneLaunch nodes the partials' area holds 256 * kDiagFields doubles and more)
+    const int blocks = one ? L.red_blocks : (int)std::min<int64_t>(1024, (L.n + kReduceThreads - 1) / kReduceThreads);
     EnergyArgs ea{d.buf[d.cur], L.n,     (int)d.cfg.nx,   L.ps,       L.rs,
-                  d.relax.rho0, rho_ref, {0.0, 0.0, 0.0}, d.partials, reinterpret_cast<unsigned *>(d.flag + 1),
-                  out};
+                  d.relax.rho0, rho_ref, {0.0, 0.0, 0.0}, d.partials,
+                  one ? reinterpret_cast<unsigned *>(d.flag + 1) : nullptr, out};
     for (int a = 0; a < L.dim; ++a)
         ea.U[a] = U ? U[a] : 0.0;
     void (*fn)(EnergyArgs) = L.dim == 1   ? (dev ? k_energy<1, true> : k_energy<1, false>)
                              : L.dim == 2 ? (dev ? k_energy<2, true> : k_energy<2, false>)
                                           : (dev ? k_energy<3, true> : k_energy<3, false>);
-    hipLaunchKernelGGL(fn, dim3((unsigned)L.red_blocks), dim3(kReduceThreads), 0, s, ea);
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kReduceThreads), 0, s, ea);
+    if (!one)
+        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kReduceThreads), 0, s, (const double *)d.partials, blocks,
+                           out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return hip_fail(e, "energy launch");
