@@ -219,7 +219,7 @@ static void (*strip1_corr(bool corr))(StripArgs) {
 template <int DT, int EQ>
 static void (*strip1_nc(bool corr, bool wide, bool nt))(StripArgs) {
     constexpr int NC = DT == kF64 ? 4 : 8;
-    if (!wide)  // (short rows fit the caches: plain stores)
+    if (!wide)  // (short rows fit the caches, and full lines gain nothing: plain stores)
         return strip1_corr<DT, EQ, 2, false>(corr);
     return nt ? strip1_corr<DT, EQ, NC, true>(corr) : strip1_corr<DT, EQ, NC, false>(corr);
 }
@@ -230,12 +230,16 @@ static void (*strip1_kernel(int eq, bool corr, bool wide, bool nt))(StripArgs) {
                                   : strip1_nc<DT, kEqEntropic>(corr, wide, nt);
 }
 
-static bool strip1_wide(int64_t nx) { return nx >= kStrip1Wide; }
+// Launches of few steps on doubles are bound by their bytes.  Two or three steps: lanes
+// of two columns, whose stores fill whole lines, beat four (us per launch of two steps
+// with the correction, four columns / two: 2^27 nodes 1657 / 1168, 2^24 211 / 148, 2^22
+// 31.9 / 30.4).
+static bool strip1_wide(int64_t nx, int dtype, int K) { return nx >= kStrip1Wide && !(dtype == kF64 && K < 4); }
 static int strip1_halo(int K) { return (K + 7) / 8 * 8; }
 
 // Columns a wavefront owns with K steps per launch.
 int strip1_cols(int64_t nx, int dtype, int K) {
-    return 64 * (strip1_wide(nx) ? (dtype == kF64 ? 4 : 8) : 2) - 2 * strip1_halo(K);
+    return 64 * (strip1_wide(nx, dtype, K) ? (dtype == kF64 ? 4 : 8) : 2) - 2 * strip1_halo(K);
 }
 
 // Most steps per launch of a run: long rows 8 (with more the halo's share grows
@@ -245,7 +249,7 @@ int strip1_cols(int64_t nx, int dtype, int K) {
 // 0.34 / 0.29 / 0.27 / 0.27, 100,000 0.48 / 0.44 / 0.42 / 0.58, 200,000 0.65 / 0.61 / 0.75,
 // 400,000 1.00 / 0.93 / 1.19, 2^20 1.95 / 2.18 / 2.56; FP32 alike).
 int strip1_steps(int64_t nx) {
-    return strip1_wide(nx) ? 8 : nx > 400000 ? 16 : nx > 2 * 1024 * 64 ? 24 : 32;
+    return nx >= kStrip1Wide ? 8 : nx > 400000 ? 16 : nx > 2 * 1024 * 64 ? 24 : 32;
 }
 
 int launch_strip1(const Layout &L, const StepArgs &s, int dtype, bool corr, int K, hipStream_t stream) {
@@ -263,7 +267,9 @@ int launch_strip1(const Layout &L, const StepArgs &s, int dtype, bool corr, int 
     a.rs = L.rs;
     a.relax = s.relax;
     a.flag = s.flag;
-    const bool wide = strip1_wide(s.nx), nt = t2_nt_stores(L.buf_bytes);
+    // (a lane's four doubles go in two stores, each of half lines, which non-temporal stores
+    // do not join: four steps 1656 us with them, 1310 without; eight 2188 and 2204)
+    const bool wide = strip1_wide(s.nx, dtype, K), nt = t2_nt_stores(L.buf_bytes) && !(dtype == kF64 && K < 8);
     void (*fn)(StripArgs) = dtype == kF64 ? strip1_kernel<kF64>(L.eq, corr, wide, nt)
                                           : strip1_kernel<kDevF64>(L.eq, corr, wide, nt);
     constexpr int per_wg = kStripThreads / 64;
