@@ -26,6 +26,9 @@ import numpy as np
 from . import lbm
 
 TILES = [(64, 4), (64, 2), (64, 1), (32, 8), (32, 2), (128, 2), (128, 1), (256, 1), (16, 16), (16, 4)]
+# name of the candidate set in cache keys: changes with the candidates and with the
+# kernels that one of them selects, so that choices made among others are not used
+CANDIDATES = "candidates-v10"
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "lbm_entropic", "autotune.json")
 
 
@@ -39,16 +42,16 @@ def candidates(persistent: bool = False):
     MI355X (every workgroup polls one device-coherent counter and does an
     agent-scope release and acquire), against a few microseconds between
     back-to-back launches, and it was the slower form on every workload
-    measured.  Two steps per launch come with three sweep lengths, and as one
-    tile-ordered persistent launch per run (no grid barrier; the two-step
-    classes only) with two."""
+    measured.  Two steps per launch come in blocks (time_rows 0) and with three
+    sweep lengths, and as one tile-ordered persistent launch per run (no grid
+    barrier; the two-step classes only) with two."""
     forms = (0, 1) if persistent else (0,)
     rows = [dict(tile_x=tx, tile_y=ty, persistent=p) for (tx, ty) in TILES for p in forms]
     flat = [dict(tile_x=tx, tile_y=ty, persistent=p, flat=1) for (tx, ty) in FLAT_TILES for p in forms]
     fit = [dict(tile_x=64, tile_y=4, persistent=p, row_fit=1) for p in forms]
-    # two steps per launch for large D2Q9 classes (the tile and row fit serve the
-    # one-step launches of the other classes), with three sweep lengths
-    two = [dict(tile_x=64, tile_y=4, persistent=0, row_fit=1, time_block=2, time_rows=r) for r in (0, 32, 64)]
+    # two steps per launch for D2Q9 classes (the tile and row fit serve the one-step
+    # launches of the other classes): blocks, and sweeps of three lengths
+    two = [dict(tile_x=64, tile_y=4, persistent=0, row_fit=1, time_block=2, time_rows=r) for r in (0, 16, 32, 64)]
     ordered = [dict(tile_x=64, tile_y=4, persistent=1, row_fit=1, time_block=2, time_rows=r) for r in (0, 32)]
     return rows + flat + fit + two + ordered
 
@@ -127,7 +130,7 @@ def tune_pool(domains, steps: int = 60, cands=None, cache_path: str | None = DEF
     "failed", each candidate that the library refused or that raised an error
     while it ran (for instance a persistent run whose grid barrier timed out),
     with the error text."""
-    key = f"candidates-v9|{_device_key()}|{signature(domains)}" if cands is None else \
+    key = f"{CANDIDATES}|{_device_key()}|{signature(domains)}" if cands is None else \
         f"custom-{hashlib.sha256(json.dumps(cands, sort_keys=True).encode()).hexdigest()[:12]}|{_device_key()}|" \
         f"{signature(domains)}"
     cache = _load_cache(cache_path) if cache_path else {}
