@@ -194,8 +194,8 @@ static T2Geom t2_geom(int64_t nx, int64_t ny, int dtype, int R, bool persistent)
     return g;
 }
 
-// Whether a class's launches of two steps take blocks (k_pool_block2) instead
-// of the sweeps above.
+// Whether a class's launches of two steps may take blocks (k_pool_block2) instead
+// of the sweeps above: unless the tuning names the sweeps' rows.
 constexpr int64_t kPoolBlockNodes = 4096;  // least nodes of a class's two-step slots
 static bool t2_blocks(const lbm_pool_tuning &t) { return !t.persistent && t.time_rows == 0; }
 
@@ -635,20 +635,26 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
         bool two = p->tun.time_block == 2 && cdim == 2 && (cdtype == kF64 || cdtype == kDevF64) &&
                    p->tun.layout == LBM_LAYOUT_ROWS;
         size_t class_buf_bytes = 0;
-        int64_t two_nodes = 0;
+        int64_t two_nodes = 0, block_nodes = 0;  // of those slots, and of their blocks' rows
         for (int i : order) {
             class_buf_bytes += p->slots[i].d.L.buf_bytes;
-            if (steps_of(i) >= 2)
+            if (steps_of(i) >= 2) {
+                const int64_t nx = p->slots[i].d.cfg.nx, ny = p->slots[i].d.cfg.ny;
                 two_nodes += p->slots[i].d.L.n;
+                block_nodes += nx * ((ny + kPoolBlockRows - 1) / kPoolBlockRows * kPoolBlockRows);
+            }
         }
-        two = two && two_nodes >= (t2_blocks(p->tun) ? kPoolBlockNodes
-                                   : cdtype == kF64  ? (int64_t)1 << 20
-                                                     : (int64_t)1 << 22);
+        // A block takes its rows whether the slot has them or not: flat classes keep the
+        // other forms (us per step, theirs / blocks: FP32 3,000,000 x 1 45 / 190, 600,000 x
+        // 5 34 / 42, 100,000 x 3 6.6 / 9.2; FP64 600,000 x 5 48 / 59, 375,000 x 8 47 / 48).
+        const bool use_blocks = t2_blocks(p->tun) && 10 * block_nodes <= 19 * two_nodes;
+        two = two && two_nodes >= (use_blocks       ? kPoolBlockNodes
+                                   : cdtype == kF64 ? (int64_t)1 << 20
+                                                    : (int64_t)1 << 22);
         const bool pers = p->tun.persistent != 0;
         const int B = t2_block(cdtype, pers), TX = t2_cols(cdtype, pers);
         const int R = t2_rows(p->tun, cdtype);
-        // launches of two steps take blocks, unless the tuning names the sweeps' rows
-        const bool blocks = two && t2_blocks(p->tun);
+        const bool blocks = two && use_blocks;
         auto geom = [&](int i) {
             const int64_t nx = p->slots[i].d.cfg.nx, ny = p->slots[i].d.cfg.ny;
             if (!blocks)
