@@ -112,10 +112,11 @@ __device__ __forceinline__ void node_moments(const double (&f)[Lattice<DIM>::Q],
 // "IA-64 and Elementary Functions", 2000, ch. 8; the same scheme as a general
 // double square root, without the scaling that inputs near the ends of the
 // exponent range need and this range does not).  The estimate's relative
-// error e is at most 2^-24, the Goldschmidt step's about 1.5 e^2 and the
-// correction's half the square of that, far below the rounding of its last
-// fused multiply-add: a second correction would change nothing but ties, and
-// the result is within one unit in the last place.  Outside [1, 4) -- a node
+// error e is at most 2^-23 (2^29 units of a double, as documented), the
+// Goldschmidt step's about 1.5 e^2 = 2^-45 and the correction's the square of
+// that, far below the rounding of its last fused multiply-add: the result is
+// within 1/2 + 2^-30 units in the last place, and a second correction would
+// change it only next to a tie.  Outside [1, 4) -- a node
 // that has left the equilibrium's domain, flagged anyway -- its value is
 // unspecified.
 __host__ __device__ __forceinline__ double sqrt_1to4(double x) {
@@ -134,8 +135,10 @@ __host__ __device__ __forceinline__ double sqrt_1to4(double x) {
 
 // 1 / x for the density of a node (x > 0 and of order 1 inside the
 // equilibrium's domain): the hardware reciprocal estimate r0 and one
-// third-order step r0 + r0 (e + e^2), e = 1 - x r0 (at most 2^-24, so that the
-// neglected e^3 is 2^-72), within one unit in the last place; for x <= 0 or
+// third-order step r0 + r0 (e + e^2), e = 1 - x r0 (at most 2^-23, so that the
+// neglected e^3 is 2^-69), within 1/2 + 2^-15 units in the last place: two
+// second-order steps round the other way for one value in some ten thousand at
+// most (none of two million measured); for x <= 0 or
 // non-finite (a node outside the domain, flagged) the value is unspecified.
 __device__ __forceinline__ double recip_density(double x) {
     const double r = __builtin_amdgcn_rcp(x);
