@@ -566,23 +566,36 @@ __device__ __forceinline__ double get_partial(const double *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Lane moves, 32 bits at a time: a value permuted by a DPP control word, and one
+// lane's value (uniform index) in every lane.
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_move(T v) {
+    if constexpr (sizeof(T) == 4) {
+        const int b = __builtin_bit_cast(int, v);
+        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, b, CTRL, 0xf, 0xf, true));
+    } else {
+        int2 b = __builtin_bit_cast(int2, v);
+        b.x = __builtin_amdgcn_update_dpp(0, b.x, CTRL, 0xf, 0xf, true);
+        b.y = __builtin_amdgcn_update_dpp(0, b.y, CTRL, 0xf, 0xf, true);
+        return __builtin_bit_cast(T, b);
+    }
+}
+template <typename T>
+__device__ __forceinline__ T read_lane(T v, int lane) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+    } else {
+        int2 b = __builtin_bit_cast(int2, v);
+        b.x = __builtin_amdgcn_readlane(b.x, lane);
+        b.y = __builtin_amdgcn_readlane(b.y, lane);
+        return __builtin_bit_cast(T, b);
+    }
+}
+
 // Fold of a value over the wavefront, the result in every lane: lane moves
 // within the rows of 16 lanes (neighbour, pair, half row and row mirrored), then the four
 // rows' results as scalars.  (Shuffles go through LDS: moments of 64^2 nodes 6.8 us
 // with them, 6.3 so.)
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-    int2 b = __builtin_bit_cast(int2, v);
-    b.x = __builtin_amdgcn_update_dpp(0, b.x, CTRL, 0xf, 0xf, true);
-    b.y = __builtin_amdgcn_update_dpp(0, b.y, CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, b);
-}
-__device__ __forceinline__ double read_lane(double v, int lane) {
-    int2 b = __builtin_bit_cast(int2, v);
-    b.x = __builtin_amdgcn_readlane(b.x, lane);
-    b.y = __builtin_amdgcn_readlane(b.y, lane);
-    return __builtin_bit_cast(double, b);
-}
 template <typename F>
 __device__ __forceinline__ double wave_fold(double v, F f) {
     v = f(v, dpp_move<0xb1>(v));   // lane ^ 1

@@ -21,41 +21,14 @@ namespace lbm {
 
 // Value of the lane above / below (0 past the end of the wavefront: those
 // columns are halo that no later step uses).
-__device__ __forceinline__ int lane_up(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
-__device__ __forceinline__ int lane_down(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
 template <bool UP, typename T>
 __device__ __forceinline__ T lane_move(T v) {
-    if constexpr (sizeof(T) == 4) {
-        const int b = __builtin_bit_cast(int, v);
-        return __builtin_bit_cast(T, UP ? lane_up(b) : lane_down(b));
-    } else {
-        const int2 b = __builtin_bit_cast(int2, v);
-        int2 r;
-        r.x = UP ? lane_up(b.x) : lane_down(b.x);
-        r.y = UP ? lane_up(b.y) : lane_down(b.y);
-        return __builtin_bit_cast(T, r);
-    }
+    return dpp_move<UP ? 0x130 : 0x138>(v);
 }
-// Value of one lane (uniform index).
-template <typename T>
-__device__ __forceinline__ T lane_read(T v, int lane) {
-    if constexpr (sizeof(T) == 4) {
-        return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-    } else {
-        int2 b = __builtin_bit_cast(int2, v);
-        b.x = __builtin_amdgcn_readlane(b.x, lane);
-        b.y = __builtin_amdgcn_readlane(b.y, lane);
-        return __builtin_bit_cast(T, b);
-    }
-}
-// g[k] <- the value that the population with c_x = cx - 1 pulls into column k.
+// g[k] <- the value that the population with c_x = cx - 1 pulls into column k (cx 0 or 2).
 template <typename T, int NC>
 __device__ __forceinline__ void pull_columns(const T (&f)[NC], int cx, T (&g)[NC]) {
-    if (cx == 1) {
-#pragma unroll
-        for (int k = 0; k < NC; ++k)
-            g[k] = f[k];
-    } else if (cx == 2) {
+    if (cx == 2) {
         const T left = lane_move<false>(f[NC - 1]);
 #pragma unroll
         for (int k = NC - 1; k > 0; --k)
@@ -513,7 +486,7 @@ __global__ __launch_bounds__(ONE ? 64 : kRowMax) void k_row1(RowArgs a) {
         T v[3] = {f[0], f[1], f[2]};
         if constexpr (ONE) {
             const T up = lane_move<true>(f[0]), down = lane_move<false>(f[2]);
-            const T head = lane_read(f[0], 0), tail = lane_read(f[2], nx - 1);
+            const T head = read_lane(f[0], 0), tail = read_lane(f[2], nx - 1);
             v[0] = right == 0 ? head : up;
             v[2] = x == 0 ? tail : down;
         } else {

@@ -627,8 +627,9 @@ static int pool_run_classes(lbm_pool *p, int64_t k, bool &any) {
         // taking at least two steps hold enough nodes.  Blocks pay at any number (us per
         // step, one step per launch / blocks: 15k nodes FP32 3.91 / 2.70, 73k 4.37 / 2.80,
         // 273k 7.18 / 4.61, 1.1M 14.99 / 10.20, 2.9M 32.2 / 21.4; FP64 15k 4.13 / 2.86, 273k
-        // 9.47 / 5.15); the smallest classes keep the launch count of one step per
-        // launch.  Sweeps need what a single domain needs for them (2048^2 FP32,
+        // 9.47 / 5.15; 40 steps of 4,032 nodes FP32 128 / 113, of 256 nodes 130 / 109); below
+        // kPoolBlockNodes a class keeps one step per launch all the same, so that
+        // lbm_pool_stats counts its launches as it did.  Sweeps need what a single domain needs for them (2048^2 FP32,
         // 1024^2 FP64; a workgroup sweeps its rows one after another): with a few
         // small slots the one-step form answers sooner (served p50 latency 44 against
         // 18 ms)
