@@ -55,16 +55,16 @@ def measured_traffic():
 
 
 VALU_PEAK_GINST = 256 * 4 * 2.4 / 4  # G wavefront-instructions/s: 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles
-VALU_PROFILE = os.path.join(ROOT, "profiles", "multistep_valu_d2q9_4096_d1q3_2e27_c4_512.md")
+VALU_PROFILE = os.path.join(ROOT, "profiles", "strips_and_blocks.md")
 
 
 def multistep_source_digest() -> str:
-    """Digest of the sources of the multi-step kernels (node arithmetic, one-step,
-    two-step and pool kernels); their counted VALU instructions are used only
-    while it matches the profile's."""
+    """Digest of the sources of the multi-step kernels (node arithmetic, two-step
+    sweeps and strips); their counted VALU instructions are used only while it
+    matches the profile's."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2303_08163_amd", "csrc")
-    for fn in ("node.hpp", "kernels.hpp", "kernels_t2.hpp", "pool_kernels.hpp", "tile_deps.hpp"):
+    for fn in ("node.hpp", "kernels.hpp", "kernels_t2.hpp", "kernels_strip.hpp"):
         with open(os.path.join(csrc, fn), "rb") as f:
             h.update(fn.encode() + b"\0" + f.read())
     return h.hexdigest()[:16]

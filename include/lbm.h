@@ -131,8 +131,9 @@ typedef struct lbm_tuning {
                                  nodes_per_thread, flags and layout left at their defaults
                                  and FP64 or FP32_DEV storage, launches take as many steps
                                  as pay: D1Q3 8 to 32 (any number on rows of up to 256
-                                 nodes), D2Q9 4 to 6, D3Q27 2 where sweeps or blocks pay; the
-                                 results are bitwise those of 1 */
+                                 nodes), D2Q9 4 to 6, D3Q27 2, each where it beats one
+                                 (lbm_get_run_info states the choice); the results are
+                                 bitwise those of 1 */
     int32_t time_rows;        /* time_block = 2: rows swept per workgroup (>= 1; 0 = default);
                                  must be 0 otherwise */
     int32_t reserved;         /* must be 0 */
@@ -455,8 +456,9 @@ typedef struct lbm_pool_tuning {
                            >= 4096 nodes; a slot whose step count in
                            the run is odd takes its last step in a one-step launch.  With
                            time_rows = 0 such a launch works in blocks of 62 x 14 nodes; with
-                           time_rows given, or persistent = 1, in sweeps, and from 2^22
-                           (FP32) or 2^20 (FP64) nodes.  Sweeps, FP32:
+                           time_rows given, persistent = 1, or slots so flat that the
+                           blocks' rows exceed 1.9 times their nodes, in sweeps, and from
+                           2^22 (FP32) or 2^20 (FP64) nodes.  Sweeps, FP32:
                            slots whose row, rounded up to 64, is at most 512 nodes (1024
                            with persistent = 1) run as whole-row tiles (no halo columns),
                            wider ones as column tiles of 512 (1024); FP64: column tiles of

@@ -81,9 +81,10 @@ struct StripVec<T, 1> {
 // population at its own source column, so K - 1 halo columns do.
 //
 // Bound: the FP64 arithmetic of the collisions with float storage (4096^2, four
-// steps: 137 VALU instructions per node update and 1.2 times the nodes, at 80 %
-// of the issue rate with three wavefronts per SIMD), arithmetic and HBM alike
-// with double (six steps).  us per step at 4096^2, against the two-step sweep
+// steps: 148 VALU instructions per node update, 1.14 times the collisions for the
+// halo included, at 71 % of the issue rate and the vector units busy for 76 % of
+// the time, three wavefronts per SIMD), arithmetic and HBM alike with double (six
+// steps).  us per step at 4096^2, against the two-step sweep
 // through LDS: FP32 117 -> 88, FP64 212 -> 95.  Two columns per lane spill
 // (543 us per launch against 358); more than 168 / 256 registers a lane would
 // be needed for five (FP32) or eight (FP64) steps at the same occupancy.  A
@@ -324,6 +325,11 @@ __global__ __launch_bounds__(64 * block_waves(RPT)) void k_block2(BlockArgs a) {
 
 // One D1Q3 wavefront: K steps (1 .. h) of the strip's own columns.  h and tx are
 // multiples of NC and of the vector width.
+//
+// Bound: VALU issue.  2^27 nodes with the correction, float storage, eight steps: 69
+// instructions per node update, halo included, 79 % of the issue rate and the
+// vector units busy for 90 % of the time in a call of 64 steps (2384 us per launch),
+// 86 and 98 % in one of 200.
 template <int DT, bool CORR, int EQ, int NC, bool NT>
 __global__ __launch_bounds__(kStripThreads) void k_strip1(StripArgs a) {
     using T = store_t<DT>;
