@@ -704,7 +704,7 @@ namespace {
 class HostBlocks {
     static constexpr int kSlab = 64, kMost = 1024;
     std::mutex lock;
-    char *spare[kMost];
+    char *spare[kMost] = {};
     int spares = 0, made = 0;
 
 public:
@@ -727,11 +727,8 @@ public:
         spare[spares++] = reinterpret_cast<char *>(block);
     }
 };
-// (never destroyed: handles may be closed while the process ends)
-HostBlocks &host_blocks() {
-    static HostBlocks *blocks = new HostBlocks();
-    return *blocks;
-}
+// (constant-initialised and without a destructor: handles may be closed while the process ends)
+HostBlocks host_blocks;
 }  // namespace
 
 // Pack: plane 0's populations with c_z = -1 into `lower`, plane nz - 1's with
@@ -845,7 +842,7 @@ int lbm_create_tuned(const lbm_config *cfg, const lbm_tuning *tuning, void *work
         set_error("initial state has a node with rho <= 0 or |u_alpha| >= 1");
         return LBM_EDOMAIN;
     }
-    h->host = host_blocks().take();
+    h->host = host_blocks.take();
     // capture the step graphs now, so that no later call pays for it
     h->graphs_off = L.deep != 0 && L.dim < 3;
     if (!L.zhalo) {
@@ -1382,7 +1379,7 @@ int lbm_destroy(lbm_handle *h) {
         keep(hipStreamDestroy(h->capture));
     // (a block that a failed stream may still write to is not used again)
     if (h->host && synced)
-        host_blocks().give(h->host);
+        host_blocks.give(h->host);
     delete h;
     if (e != hipSuccess)
         return hip_fail(e, "destroy synchronise");
