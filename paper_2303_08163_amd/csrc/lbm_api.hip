@@ -1026,7 +1026,9 @@ int lbm_step(lbm_handle *h, int64_t nsteps) {
             d.steps += kGraphSteps;  // an even count of swaps: d.cur is unchanged
         }
     }
-    const int64_t plain = s + (d.L.deep && is_capturing(h->stream) ? captured_prefix(d.L, nsteps - s) : 0);
+    int64_t plain = s + (d.L.deep ? captured_prefix(d.L, nsteps - s) : 0);
+    if (plain > s && !is_capturing(h->stream))
+        plain = s;
     while (s < nsteps) {
         const int K = s < plain ? (plain - s >= d.L.tblock ? d.L.tblock : 1) : next_steps(d.L, nsteps - s);
         int rc = enqueue_steps(h, d.cur, K, h->stream);
@@ -1182,8 +1184,8 @@ int lbm_energy_history(lbm_handle *h, int64_t steps, int64_t every, const double
     }
     // (not into a caller's graph that would find the state elsewhere at a replay, see captured_prefix)
     if (h->d.L.row && steps > 0 && row1_history(h->d.cfg.nx, every) &&
-        !(is_capturing(h->stream) &&
-          (row_launches(steps, every) - steps / every * plain_launches(h->d.L, every)) % 2 != 0))
+        ((row_launches(steps, every) - steps / every * plain_launches(h->d.L, every)) % 2 == 0 ||
+         !is_capturing(h->stream)))
         return row_history(h, steps, every, U, rho_ref, out);
     int rc = lbm_energy(h, U, rho_ref, out);  // also checks U and rho_ref
     for (int64_t k = 1; rc == LBM_OK && k <= steps / every; ++k) {
